@@ -91,7 +91,6 @@ struct sphfilt_batch_s {
     double *d_fc = nullptr;
     int fused = 1;                     // fused items for patches that allow them
     BatchPatchDev *d_patches = nullptr;
-    double *d_eneg = nullptr;
     std::map<int, Twiddle *> d_tw;
     int n_shells_total = 0;
     int *d_counters = nullptr;
@@ -296,8 +295,7 @@ int record(sphfilt_batch b, const ModeWork &m, int split, int wpc_setting, const
     const int spin = wait_fault ? kFaultSpinLimit : kSpinLimit, bias = wait_fault ? 1 : 0;
     auto go = [&](int first, int n, int *ticket, int deps, hipStream_t st) {
         return launch_batch(grid, m.d_work + first, n, b->d_patches, sc.ins, sc.outs, b->d_th,
-                            b->d_ph, b->d_fc, m.d_shells, sc.counters, m.d_need, ticket, sc.error,
-                            b->d_eneg, deps, spin, bias, b->variant, st);
+                            b->d_ph, b->d_fc, m.d_shells, sc.counters, m.d_need, ticket, sc.error, deps, spin, bias, b->variant, st);
     };
     hipError_t e = launch_batch_reset(sc.counters, b->n_shells_total, sc.tickets, 3, sc.error, s);
     if (e != hipSuccess) return SPHFILT_EDEVICE;
@@ -405,7 +403,7 @@ void free_batch(sphfilt_batch b)
     free_work(b);
     for (auto &kv : b->d_tw) (void)hipFree(kv.second);
     b->d_tw.clear();
-    void *ptrs[] = {b->d_th, b->d_ph, b->d_fc, b->d_patches, b->d_eneg, b->d_counters, b->d_tickets,
+    void *ptrs[] = {b->d_th, b->d_ph, b->d_fc, b->d_patches, b->d_counters, b->d_tickets,
                     b->d_error};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -873,7 +871,6 @@ int sphfilt_batch_create(sphfilt_batch *out, int n_patches, const sphfilt_patch_
         if (!rc) rc = upload(&b->d_fc, all_fc);
         if (!rc) rc = upload(&b->d_patches, pdev);
         if (!rc) b->pdev = pdev;
-        if (!rc) rc = upload(&b->d_eneg, exp_table());
         if (!rc) rc = upload(&b->d_counters, std::vector<int>((size_t)std::max(1, b->n_shells_total), 0));
         if (!rc) rc = upload(&b->d_tickets, std::vector<int>(3, 0));
         if (!rc) rc = upload(&b->d_error, std::vector<int>(1, 0));

@@ -63,7 +63,6 @@ struct BatchArgs {
     const int *need;
     int *ticket;
     int *error;
-    const double *eneg;
     int use_deps;
     int spin_limit;
     int need_bias;        // added to every wait target (0; 1 only to force a give-up in tests)
@@ -93,7 +92,7 @@ hipError_t launch_batch(int grid, const BatchWork *work, int n_work, const Batch
                         const double *const *ins, double *const *outs, const ThetaItem *th,
                         const PhiItem *ph, const double *fc, const int *shells, int *counters,
                         const int *need,
-                        int *ticket, int *error, const double *eneg, int use_deps, int spin_limit,
+                        int *ticket, int *error, int use_deps, int spin_limit,
                         int need_bias, int variant, hipStream_t s);
 // (the persistent form, grid > 0, with use_deps defers its signals; see
 // flush_pending in batch_kernels.h)

@@ -87,48 +87,44 @@ __device__ __forceinline__ int opaque_lane(int lane)
 template <int N, bool HYB>
 __device__ __forceinline__ void theta_item(const BatchWork &w, const BatchPatchDev &pd,
                                            const double *src, double *dst,
-                                           const ThetaItem *th, const double *eneg, double *lds,
-                                           double *etab, int *flags, int lane)
+                                           const ThetaItem *th, double *lds, int *flags, int lane)
 {
     for (int k = 0; k < w.count; ++k)
         theta_block<N, lines_per_256<N>(), HYB>(src, dst, th + w.first, w.n_valid, pd.cp_log2,
-                                               w.tile + k, pd.n_theta, pd.n_phi, pd.tw_theta, eneg,
-                                               lds, etab, flags, batch_hybrid(pd), opaque_lane(lane));
+                                               w.tile + k, pd.n_theta, pd.n_phi, pd.tw_theta,
+                                               lds, flags, batch_hybrid(pd), opaque_lane(lane));
 }
 
 template <int N, bool HYB>
 __device__ __forceinline__ void phi_item(const BatchWork &w, const BatchPatchDev &pd,
-                                         const double *src, double *dst, const PhiItem *ph,
-                                         const double *eneg, double *lds, double *etab, int *flags,
+                                         const double *src, double *dst, const PhiItem *ph, double *lds, int *flags,
                                          int lane)
 {
     constexpr int L = lines_per_256<N>();
     for (int g = 0; g < w.n_valid; g += L)
         phi_block<N, L, HYB>(src, dst, ph + w.first + g, min(L, w.n_valid - g), pd.n_theta,
-                             pd.tw_phi, eneg, lds, etab, flags, batch_hybrid(pd), opaque_lane(lane));
+                             pd.tw_phi, lds, flags, batch_hybrid(pd), opaque_lane(lane));
 }
 
 template <int N, bool HYB>
 __device__ __forceinline__ void fused_item(const BatchWork &w, const BatchPatchDev &pd,
                                            const double *src, double *dst, const ThetaItem *th,
-                                           const double *fc, const double *eneg, double *lds,
-                                           double *etab, int *flags, int lane)
+                                           const double *fc, double *lds, int *flags, int lane)
 {
     const HybridArgs h = batch_hybrid(pd);
     if (w.tile)
-        shell_block<N, true, HYB>(src, dst, th + w.first, fc + w.aux, w.n_valid, pd.tw_phi, eneg,
-                                  lds, etab, flags, h, h, lane);
+        shell_block<N, true, HYB>(src, dst, th + w.first, fc + w.aux, w.n_valid, pd.tw_phi,
+                                  lds, flags, h, h, lane);
     else
-        shell_block<N, false, HYB>(src, dst, th + w.first, fc + w.aux, w.n_valid, pd.tw_phi, eneg,
-                                   lds, etab, flags, h, h, lane);
+        shell_block<N, false, HYB>(src, dst, th + w.first, fc + w.aux, w.n_valid, pd.tw_phi,
+                                   lds, flags, h, h, lane);
 }
 
 // One work item k (workgroup-uniform): wait for its shells (second pass),
 // filter, signal its shells (first pass).
 // gave_up: a workgroup-shared word for the outcome of the wait.
 template <bool HYB, bool MIXED>
-__device__ __forceinline__ void run_item(const BatchArgs &a, int k, int lane, double *lds,
-                                         double *etab, int *flags, int *gave_up)
+__device__ __forceinline__ void run_item(const BatchArgs &a, int k, int lane, double *lds, int *flags, int *gave_up)
 {
     const BatchWork w = a.work[k];
     const BatchPatchDev pd = a.patches[w.patch];
@@ -165,47 +161,47 @@ __device__ __forceinline__ void run_item(const BatchArgs &a, int k, int lane, do
     double *dst = a.outs[w.patch];
     if (w.pass == 0) {
         switch (pd.n_line) {
-        case 32: theta_item<32, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-        case 64: theta_item<64, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-        case 128: theta_item<128, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
+        case 32: theta_item<32, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+        case 64: theta_item<64, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+        case 128: theta_item<128, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
         default:
             if constexpr (MIXED) {
                 switch (pd.n_line) {
-                case 48: theta_item<48, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-                case 80: theta_item<80, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-                case 96: theta_item<96, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-                case 160: theta_item<160, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-                case 192: theta_item<192, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
-                default: theta_item<256, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane); break;
+                case 48: theta_item<48, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+                case 80: theta_item<80, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+                case 96: theta_item<96, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+                case 160: theta_item<160, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+                case 192: theta_item<192, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
+                default: theta_item<256, HYB>(w, pd, src, dst, a.th, lds, flags, lane); break;
                 }
             } else {
-                theta_item<256, HYB>(w, pd, src, dst, a.th, a.eneg, lds, etab, flags, lane);
+                theta_item<256, HYB>(w, pd, src, dst, a.th, lds, flags, lane);
             }
             break;
         }
     } else if (w.pass == 2) {
         switch (pd.n_phi) {
-        case 32: fused_item<32, HYB>(w, pd, src, dst, a.th, a.fc, a.eneg, lds, etab, flags, lane); break;
-        case 64: fused_item<64, HYB>(w, pd, src, dst, a.th, a.fc, a.eneg, lds, etab, flags, lane); break;
-        default: fused_item<128, HYB>(w, pd, src, dst, a.th, a.fc, a.eneg, lds, etab, flags, lane); break;
+        case 32: fused_item<32, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
+        case 64: fused_item<64, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
+        default: fused_item<128, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
         }
     } else {
         switch (pd.n_phi) {
-        case 32: phi_item<32, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-        case 64: phi_item<64, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-        case 128: phi_item<128, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
+        case 32: phi_item<32, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+        case 64: phi_item<64, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+        case 128: phi_item<128, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
         default:
             if constexpr (MIXED) {
                 switch (pd.n_phi) {
-                case 48: phi_item<48, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-                case 80: phi_item<80, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-                case 96: phi_item<96, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-                case 160: phi_item<160, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-                case 192: phi_item<192, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
-                default: phi_item<256, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane); break;
+                case 48: phi_item<48, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+                case 80: phi_item<80, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+                case 96: phi_item<96, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+                case 160: phi_item<160, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+                case 192: phi_item<192, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
+                default: phi_item<256, HYB>(w, pd, src, dst, a.ph, lds, flags, lane); break;
                 }
             } else {
-                phi_item<256, HYB>(w, pd, src, dst, a.ph, a.eneg, lds, etab, flags, lane);
+                phi_item<256, HYB>(w, pd, src, dst, a.ph, lds, flags, lane);
             }
             break;
         }
@@ -289,11 +285,10 @@ template <bool HYB, bool MIXED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(oneshot_waves<HYB, MIXED>()))) void batch_kernel_oneshot(BatchArgs a)
 {
     __shared__ double lds[batch_lds<HYB, MIXED>()];
-    __shared__ double etab[129];
     __shared__ int flags[64];
     __shared__ int cur, gave_up;
     const int k = a.use_deps ? next_ticket(a.ticket, &cur) : (int)blockIdx.x;
-    if (k < a.n_work) run_item<HYB, MIXED>(a, k, threadIdx.x, lds, etab, flags, &gave_up);
+    if (k < a.n_work) run_item<HYB, MIXED>(a, k, threadIdx.x, lds, flags, &gave_up);
 }
 
 // Persistent form: a fixed grid; each workgroup takes tickets until the list
@@ -305,7 +300,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(persistent_
     BatchArgs a)
 {
     __shared__ double lds[batch_lds<HYB, MIXED>()];
-    __shared__ double etab[129];
     __shared__ int flags[64];
     __shared__ int cur, gave_up;
     __shared__ int pending[kPendingItems], n_pending;
@@ -328,7 +322,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(persistent_
                 const BatchWork &w = a.work[k];
                 if (w.second || n_pending == kPendingItems) flush_pending(a, pending, &n_pending, (int)lane);
             }
-            run_item<HYB, MIXED>(a, k, (int)lane, lds, etab, flags, &gave_up);
+            // every wave is done with the last item's LDS
+            __syncthreads();
+            run_item<HYB, MIXED>(a, k, (int)lane, lds, flags, &gave_up);
             if (a.defer && !a.work[k].second && a.work[k].n_shells > 0) {
                 __syncthreads();
                 if (lane == 0) pending[n_pending++] = k;

@@ -5,18 +5,23 @@
 //
 //   X[k1 + N1 k2] = sum_n2 W_N2^{n2 k2} W_N^{n2 k1} sum_n1 x[N2 n1 + n2] W_N1^{n1 k1}
 //
-// done as: an N1-point DFT in registers, a twiddle by W_N^{t k1}, one LDS
-// transpose, ceil(N1/N2) rows of N2-point DFTs per lane in registers (the
-// last row partly padding when N2 does not divide N1); then the mask; then
-// the same steps in reverse (inverse DFTs, conjugate twiddles, one LDS
-// transpose) so that every lane ends up with its own N1 input positions again.
-// Two HBM touches per line (load, store) and two LDS transposes in between.
+// done as: an N1-point DFT in registers, one LDS transpose, ceil(N1/N2) rows
+// of N2-point DFTs per lane in registers that carry the twiddles W_N^{n2 k1}
+// in their butterflies (the last row partly padding when N2 does not divide
+// N1); then the mask; then inverse N2-point DFTs, one LDS transpose back and
+// inverse N1-point DFTs that carry the conjugate twiddles, so that every lane
+// ends up with its own N1 input positions again.  Two HBM touches per line
+// (load, store) and two LDS transposes in between.
 //
-// The small in-register DFTs are radix-2 decimation in frequency with their
-// twiddles as compile-time constants, with one radix-3 or radix-5 stage in
-// front for sizes 3 * 2^k and 5 * 2^k; the output permutations are register
-// renamings, so they cost nothing.
+// The small in-register DFTs are radix-2 decimation in time, with one radix-3
+// or radix-5 stage in front for sizes 3 * 2^k and 5 * 2^k; the permutations
+// are register renamings, so they cost nothing.  A butterfly a +- w b with
+// w = cos(x) (1 -+ i tan(x)) is six fused multiply-adds (b' = b -+ i tan(x) b,
+// then a +- cos(x) b'), where a complex multiply and two complex additions
+// are eight operations.
 #pragma once
+#include "sphfilt_internal.h"
+
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -87,35 +92,53 @@ constexpr int bitrev(int x, int bits)
     return r;
 }
 
-// a * W_M^I with W_M = exp(-2 pi i / M) (forward) or exp(+2 pi i / M) (INV).
-// M divides 64; trivial factors (1, -1, +-i, (+-1 +-i)/sqrt2) take no multiply
-// by a general constant.
+// a' = a + w b, b' = a - w b with w = W_M^I = exp(-2 pi i I / M) (forward) or
+// its conjugate (INV).  M divides 64, I < M / 2.  Angles past pi/2 take a
+// factor -+i (a renaming and a sign); the tangent (up to pi/4) or cotangent
+// (above) of the rest is a compile-time constant of at most 1.
 template <int M, int I, bool INV>
-__device__ __forceinline__ cplx twiddle_const(cplx a)
+__device__ __forceinline__ void butterfly_const(cplx &a, cplx &b)
 {
-    static_assert(64 % M == 0, "twiddle order must divide 64");
-    constexpr int ang = ((64 / M) * I) % 64;             // angle = ang * pi / 32
-    constexpr int e = INV ? ang : (64 - ang) % 64;       // exp(i e pi / 32)
-    if constexpr (e == 0) {
-        return a;
-    } else if constexpr (e == 32) {
-        return {-a.re, -a.im};
-    } else if constexpr (e == 16) {                      // * i
-        return {-a.im, a.re};
-    } else if constexpr (e == 48) {                      // * -i
-        return {a.im, -a.re};
-    } else if constexpr (e % 16 == 8) {                  // * (+-1 +-i)/sqrt2
-        constexpr double h = 0.7071067811865475244008444;
-        constexpr double cr = cos_pi32(e) > 0 ? h : -h;
-        constexpr double ci = sin_pi32(e) > 0 ? h : -h;
-        if constexpr (cr == ci)
-            return {cr * (a.re - a.im), cr * (a.re + a.im)};
-        else
-            return {cr * (a.re + a.im), cr * (a.im - a.re)};
-    } else {
-        constexpr double c = cos_pi32(e), s = sin_pi32(e);
-        return {a.re * c - a.im * s, a.re * s + a.im * c};
+    static_assert(64 % M == 0 && I < M / 2, "twiddle order must divide 64");
+    constexpr int ang = (64 / M) * I;                    // angle = ang * pi / 32 < pi
+    constexpr int r = ang % 16;                          // ... modulo pi / 2
+    cplx x = b;
+    constexpr double scale = r <= 8 ? cos_pi32(r) : sin_pi32(r);
+    if constexpr (r != 0) {
+        // b times (1 -+ i tan r), or (cot r -+ i): w b = scale * x
+        constexpr double s = INV ? -1.0 : 1.0;
+        if constexpr (r == 8) {
+            x = cplx{b.re + s * b.im, b.im - s * b.re};
+        } else if constexpr (r < 8) {
+            constexpr double tn = s * (sin_pi32(r) / cos_pi32(r));
+            x = cplx{__builtin_fma(tn, b.im, b.re), __builtin_fma(-tn, b.re, b.im)};
+        } else {
+            constexpr double ctn = cos_pi32(r) / sin_pi32(r);
+            x = cplx{__builtin_fma(ctn, b.re, s * b.im), __builtin_fma(ctn, b.im, -s * b.re)};
+        }
     }
+    if constexpr (ang >= 16) x = INV ? cplx{-x.im, x.re} : cplx{x.im, -x.re};
+    const cplx a0 = a;
+    if constexpr (r == 0) {
+        a = cadd(a0, x);
+        b = csub(a0, x);
+    } else {
+        a = cplx{__builtin_fma(scale, x.re, a0.re), __builtin_fma(scale, x.im, a0.im)};
+        b = cplx{__builtin_fma(-scale, x.re, a0.re), __builtin_fma(-scale, x.im, a0.im)};
+    }
+}
+
+// The same with a twiddle known at run time: w = c (1 - i tn) (forward) or its
+// conjugate (INV), times -i (forward) or +i (INV) with QUARTER.
+template <bool QUARTER, bool INV>
+__device__ __forceinline__ void butterfly_tan(cplx &a, cplx &b, double c, double tn)
+{
+    const double t = INV ? -tn : tn;
+    cplx x = {__builtin_fma(t, b.im, b.re), __builtin_fma(-t, b.re, b.im)};
+    if constexpr (QUARTER) x = INV ? cplx{-x.im, x.re} : cplx{x.im, -x.re};
+    const cplx a0 = a;
+    a = cplx{__builtin_fma(c, x.re, a0.re), __builtin_fma(c, x.im, a0.im)};
+    b = cplx{__builtin_fma(-c, x.re, a0.re), __builtin_fma(-c, x.im, a0.im)};
 }
 
 // cos(a pi / D) for D = 12 (a in [0, 6]: (sqrt6 +- sqrt2)/4, sqrt3/2,
@@ -270,31 +293,73 @@ __device__ __forceinline__ void dft_reg(cplx (&v)[NV])
     static_assert(R % 3 == 0 || R % 5 == 0 || ((R & (R - 1)) == 0 && R >= 1 && R <= 64),
                   "radix must be a power of two <= 64");
     if constexpr (R > 1 && R % 3 != 0 && R % 5 != 0) {
-        // decimation in frequency: spans R/2, R/4, ..., 1; output bit-reversed
+        // decimation in time on bit-reversed inputs (a register renaming),
+        // half sizes 1, 2, ..., R/2; natural order out
+        cplx x[R];
+        static_for<0, R>([&](auto kk) {
+            constexpr int k = decltype(kk)::value;
+            x[k] = v[OFF + STRIDE * bitrev(k, ilog2(R))];
+        });
         static_for<0, ilog2(R)>([&](auto st) {
-            constexpr int span = R >> (decltype(st)::value + 1);
-            static_for<0, R / (2 * span)>([&](auto bb) {
-                static_for<0, span>([&](auto ii) {
-                    constexpr int i = decltype(ii)::value;
-                    constexpr int p = OFF + STRIDE * (decltype(bb)::value * 2 * span + i);
-                    constexpr int q = p + STRIDE * span;
-                    cplx a = v[p], b = v[q];
-                    v[p] = cadd(a, b);
-                    v[q] = twiddle_const<2 * span, i, INV>(csub(a, b));
+            constexpr int h = 1 << decltype(st)::value;
+            static_for<0, R / (2 * h)>([&](auto bb) {
+                static_for<0, h>([&](auto jj) {
+                    constexpr int j = decltype(jj)::value, p = 2 * h * decltype(bb)::value + j;
+                    butterfly_const<2 * h, j, INV>(x[p], x[p + h]);
                 });
             });
         });
-        // bit-reversed -> natural: a register renaming after unrolling
-        cplx tmp[R];
         static_for<0, R>([&](auto kk) {
             constexpr int k = decltype(kk)::value;
-            tmp[k] = v[OFF + STRIDE * bitrev(k, ilog2(R))];
-        });
-        static_for<0, R>([&](auto kk) {
-            constexpr int k = decltype(kk)::value;
-            v[OFF + STRIDE * k] = tmp[k];
+            v[OFF + STRIDE * k] = x[k];
         });
     }
+}
+
+// The M-point DFT of v[OFF + n] w^n, w = W_N^k (INV: everything conjugate), M
+// a power of two dividing N and 0 <= k < N / M: the second stage of the
+// four-step transform with its twiddles inside.  Level h (half size) of the
+// decimation in time multiplies its odd halves by W_N^{k M/(2h)} W_{2h}^j, so
+// the twiddles cost no operation beyond the butterflies' own six (eight at
+// h = 1, whose angle passes pi/2): 208 operations at M = 16, where the
+// factors' powers (36), the multiplication (60) and the plain transform (168)
+// took 264.  tw: W_N^i, i < N, then cos and tan of 2 pi i / N, i < N/4, in
+// .re and .im (host_tables.cpp); j and j + h/2 share an entry.
+template <int N, int M, bool INV, int OFF = 0, int NV>
+__device__ __forceinline__ void dft_twisted(cplx (&v)[NV], int k, const Twiddle *__restrict__ tw)
+{
+    static_assert((M & (M - 1)) == 0 && M >= 4 && N % M == 0 && N % 4 == 0, "power-of-two stage");
+    cplx x[M];
+    static_for<0, M>([&](auto kk) {
+        constexpr int i = decltype(kk)::value;
+        x[i] = v[OFF + bitrev(i, ilog2(M))];
+    });
+    const Twiddle w1 = tw[k * (M / 2)];
+    const double wi = INV ? -w1.im : w1.im;
+    static_for<0, M / 2>([&](auto bb) {
+        constexpr int p = 2 * decltype(bb)::value;
+        const cplx a = x[p], b = x[p + 1];
+        x[p] = cplx{__builtin_fma(-wi, b.im, __builtin_fma(w1.re, b.re, a.re)),
+                    __builtin_fma(wi, b.re, __builtin_fma(w1.re, b.im, a.im))};
+        x[p + 1] = cplx{__builtin_fma(wi, b.im, __builtin_fma(-w1.re, b.re, a.re)),
+                        __builtin_fma(-wi, b.re, __builtin_fma(-w1.re, b.im, a.im))};
+    });
+    static_for<1, ilog2(M)>([&](auto st) {
+        constexpr int h = 1 << decltype(st)::value;
+        static_for<0, h / 2>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            const Twiddle w = tw[N + k * (M / (2 * h)) + j * (N / (2 * h))];
+            static_for<0, M / (2 * h)>([&](auto bb) {
+                constexpr int p = 2 * h * decltype(bb)::value + j;
+                butterfly_tan<false, INV>(x[p], x[p + h], w.re, w.im);
+                butterfly_tan<true, INV>(x[p + h / 2], x[p + h / 2 + h], w.re, w.im);
+            });
+        });
+    });
+    static_for<0, M>([&](auto kk) {
+        constexpr int i = decltype(kk)::value;
+        v[OFF + i] = x[i];
+    });
 }
 
 }  // namespace sphfilt

@@ -1,7 +1,6 @@
 // host_tables.cpp -- host-side tables shared by plans and batches:
 // validation, the per-shell / per-ring-pair item lists with their cutoffs
-// (arXiv:2305.01537, Sec. II.A, the l_max / m_max equations), twiddles and
-// the e^{-k} table of the exponential mask.
+// (arXiv:2305.01537, Sec. II.A, the l_max / m_max equations) and twiddles.
 #include "host_tables.h"
 
 #include <hip/hip_runtime.h>
@@ -53,21 +52,14 @@ static void unit_root(long long j, long long N, double *c, double *s)
 
 std::vector<Twiddle> twiddles(int N)
 {
-    std::vector<Twiddle> t((size_t)N);
+    std::vector<Twiddle> t((size_t)(N + N / 4));
     for (int j = 0; j < N; ++j) {
         double c, s;
         unit_root(j, N, &c, &s);
         t[(size_t)j] = Twiddle{c, -s};
+        if (j < N / 4) t[(size_t)(N + j)] = Twiddle{c, s / c};
     }
     return t;
-}
-
-// e^{-k}, k in [0, kExpTable): the exponential mask above its cutoff.
-std::vector<double> exp_table()
-{
-    std::vector<double> e((size_t)kExpTable);
-    for (int k = 0; k < kExpTable; ++k) e[(size_t)k] = std::exp(-(double)k);
-    return e;
 }
 
 int validate(int n_r, int n_theta, int n_phi, int n_fields, const int *parity,

@@ -33,10 +33,9 @@ struct HostTables {
 
 bool fault(const char *what);
 bool supported_line(int n);
-// exp(-2 pi i j / N) for j in [0, N)
+// exp(-2 pi i j / N) for j in [0, N), then (cos, tan) of 2 pi j / N for
+// j in [0, N/4): the table of the line transforms (fft_core.h, dft_twisted)
 std::vector<Twiddle> twiddles(int N);
-// e^{-k} for k in [0, kExpTable)
-std::vector<double> exp_table();
 int validate(int n_r, int n_theta, int n_phi, int n_fields, const int *parity,
              const sphfilt_cutoff *cut);
 void build_items(int n_r, int n_theta, int n_phi, int n_fields, const int *parity,

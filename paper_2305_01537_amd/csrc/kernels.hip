@@ -20,25 +20,22 @@ template <int N, bool ADJ, bool HYB, bool MFMA, int W>
 __global__ __launch_bounds__(W) void shell_phi_kernel(
     const double *in, double *out, const ThetaItem *__restrict__ shells,
     const double *__restrict__ ring_c, int n_shells, int shell_groups,
-    const PhiItem *__restrict__ rings, int n_rings, const Twiddle *__restrict__ tw,
-    const double *__restrict__ eneg, HybridArgs ht, HybridArgs hp)
+    const PhiItem *__restrict__ rings, int n_rings, const Twiddle *__restrict__ tw, HybridArgs ht, HybridArgs hp)
 {
     using S = ShellShape<N, W>;
     constexpr int LINES = W / Split<N>::N2;
     static_assert(S::lds >= LINES * line_stride<Split<N>::N1, Split<N>::N2, HYB>(), "ring-pair scratch");
     __shared__ double lds[S::lds];
-    __shared__ double etab[N / 2 + 1];
     __shared__ int flags[LINES];
     __shared__ double gaux[MFMA ? shell_gemm_aux<N>() : 1];
     if ((int)blockIdx.x < shell_groups) {
         const int first = blockIdx.x * S::shells;
         shell_block<N, ADJ, HYB, MFMA, W>(in, out, shells + first, ring_c + (size_t)first * S::lines,
-                                       min(S::shells, n_shells - first), tw, eneg, lds, etab,
+                                       min(S::shells, n_shells - first), tw, lds,
                                        flags, ht, hp, threadIdx.x, gaux);
     } else {
         const int first = ((int)blockIdx.x - shell_groups) * LINES;
-        phi_block<N, LINES, HYB>(in, out, rings + first, min(LINES, n_rings - first), N / 2, tw,
-                                 eneg, lds, etab, flags, hp, threadIdx.x);
+        phi_block<N, LINES, HYB>(in, out, rings + first, min(LINES, n_rings - first), N / 2, tw, lds, flags, hp, threadIdx.x);
     }
 }
 
@@ -51,20 +48,17 @@ __global__ __launch_bounds__(W) void shell_phi_kernel(
 template <int N>
 __global__ __launch_bounds__(256) void theta_gemm_kernel(const double *in, double *out,
                                                          const ThetaItem *__restrict__ items,
-                                                         int n_items, const Twiddle *__restrict__ tw,
-                                                         const double *__restrict__ eneg)
+                                                         int n_items, const Twiddle *__restrict__ tw)
 {
     using S = ShellShape<N>;
     constexpr int K = N / 2, SH = S::shells;
     constexpr size_t shell_pts = (size_t)N * N / 2;
     __shared__ double lds[S::lds];
-    __shared__ double etab[N / 2 + 1];
     __shared__ double gaux[shell_gemm_aux<N>()];
     const int lane = threadIdx.x;
     const int first = blockIdx.x * SH;
     const int n_valid = min(SH, n_items - first);
     const ThetaItem *it = items + first;
-    stage_exp_table<N>(etab, eneg, lane);
     const int us = lane / S::lanes;
     const bool valid_s = us < n_valid;
     const size_t base_s = valid_s ? (size_t)it[us].shell * shell_pts : 0;
@@ -72,7 +66,7 @@ __global__ __launch_bounds__(256) void theta_gemm_kernel(const double *in, doubl
     shell_stage<N, true>(in, out, lds + us * S::stride, v, base_s, valid_s, lane % S::lanes);
     __syncthreads();
     double *fq = gaux, *cosd = gaux + SH * (N / 2 + 1), *cvec = cosd + N;
-    shell_circulants<N, SH>(it, n_valid, tw, etab, fq, cosd, cvec, lane);
+    shell_circulants<N, SH>(it, n_valid, tw, fq, cosd, cvec, lane);
     auto sign = [&](int sh) { return (it[sh].flags & kFlagOddParity) ? -1.0 : 1.0; };
     dv4 acc[gemm_tiles_per_wave<N, SH>()];
     shell_gemm<N, SH>(cvec, n_valid, lane, acc, [&](int sh, int m, int k, bool first_half) {
@@ -176,7 +170,7 @@ int shells_per_group(int n_phi)
 template <int N, bool ADJ, bool HYB, bool MFMA>
 static hipError_t shell_phi_launch(const double *in, double *out, const ThetaItem *shells,
                                    const double *ring_c, int n_shells, const PhiItem *rings,
-                                   int n_rings, const Twiddle *tw, const double *eneg,
+                                   int n_rings, const Twiddle *tw,
                                    const HybridArgs &ht, const HybridArgs &hp, hipStream_t s)
 {
     constexpr int W = N <= 64 && !MFMA && !HYB ? 128 : 256;
@@ -184,7 +178,7 @@ static hipError_t shell_phi_launch(const double *in, double *out, const ThetaIte
     const int groups = (n_shells + ShellShape<N, W>::shells - 1) / ShellShape<N, W>::shells;
     const dim3 grid((unsigned)(groups + (n_rings + LINES - 1) / LINES)), block(W);
     shell_phi_kernel<N, ADJ, HYB, MFMA, W><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells,
-                                                                  groups, rings, n_rings, tw, eneg,
+                                                                  groups, rings, n_rings, tw,
                                                                   ht, hp);
     return hipGetLastError();
 }
@@ -192,14 +186,13 @@ static hipError_t shell_phi_launch(const double *in, double *out, const ThetaIte
 template <int N, bool MFMA>
 static hipError_t shell_phi_go(bool adjoint, const double *in, double *out,
                                const ThetaItem *shells, const double *ring_c, int n_shells,
-                               const PhiItem *rings, int n_rings, const Twiddle *tw,
-                               const double *eneg, const HybridArgs &ht, const HybridArgs &hp,
+                               const PhiItem *rings, int n_rings, const Twiddle *tw, const HybridArgs &ht, const HybridArgs &hp,
                                hipStream_t s)
 {
     const bool hyb = ht.present != 0;
 #define SPHFILT_SHELL_PHI(A, H)                                                                    \
     return shell_phi_launch<N, A, H, MFMA && !H>(in, out, shells, ring_c, n_shells, rings, n_rings, \
-                                                 tw, eneg, ht, hp, s)
+                                                 tw, ht, hp, s)
     if (adjoint) {
         if (hyb) SPHFILT_SHELL_PHI(true, true); else SPHFILT_SHELL_PHI(true, false);
     } else {
@@ -215,8 +208,7 @@ bool theta_gemm_ok(int n_theta, int n_phi)
 
 hipError_t launch_shell_phi(bool adjoint, int n_theta, int n_phi, const double *in, double *out,
                             const ThetaItem *shells, const double *ring_c, int n_shells,
-                            const PhiItem *rings, int n_rings, const Twiddle *tw,
-                            const double *eneg, const HybridArgs &ht, const HybridArgs &hp,
+                            const PhiItem *rings, int n_rings, const Twiddle *tw, const HybridArgs &ht, const HybridArgs &hp,
                             hipStream_t s, bool mfma)
 {
     if (n_shells < 0 || n_rings < 0 || !shell_fusable(n_theta, n_phi)) return hipErrorInvalidValue;
@@ -224,28 +216,27 @@ hipError_t launch_shell_phi(bool adjoint, int n_theta, int n_phi, const double *
     if (n_shells + n_rings == 0) return hipSuccess;
     switch (n_phi) {
     case 32:
-        return mfma ? shell_phi_go<32, true>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, eneg, ht, hp, s)
-                    : shell_phi_go<32, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, eneg, ht, hp, s);
+        return mfma ? shell_phi_go<32, true>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s)
+                    : shell_phi_go<32, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s);
     case 64:
-        return mfma ? shell_phi_go<64, true>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, eneg, ht, hp, s)
-                    : shell_phi_go<64, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, eneg, ht, hp, s);
-    case 128: return shell_phi_go<128, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, eneg, ht, hp, s);
+        return mfma ? shell_phi_go<64, true>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s)
+                    : shell_phi_go<64, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s);
+    case 128: return shell_phi_go<128, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_theta_gemm(int n_theta, int n_phi, const double *in, double *out,
-                             const ThetaItem *items, int n_items, const Twiddle *tw,
-                             const double *eneg, hipStream_t s)
+                             const ThetaItem *items, int n_items, const Twiddle *tw, hipStream_t s)
 {
     if (n_items <= 0) return hipSuccess;
     if (!theta_gemm_ok(n_theta, n_phi)) return hipErrorInvalidValue;
     if (n_phi == 32) {
         const unsigned g = (unsigned)((n_items + ShellShape<32>::shells - 1) / ShellShape<32>::shells);
-        theta_gemm_kernel<32><<<g, 256, 0, s>>>(in, out, items, n_items, tw, eneg);
+        theta_gemm_kernel<32><<<g, 256, 0, s>>>(in, out, items, n_items, tw);
     } else {
         const unsigned g = (unsigned)((n_items + ShellShape<64>::shells - 1) / ShellShape<64>::shells);
-        theta_gemm_kernel<64><<<g, 256, 0, s>>>(in, out, items, n_items, tw, eneg);
+        theta_gemm_kernel<64><<<g, 256, 0, s>>>(in, out, items, n_items, tw);
     }
     return hipGetLastError();
 }

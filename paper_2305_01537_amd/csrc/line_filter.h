@@ -144,7 +144,8 @@ __device__ __forceinline__ void st_two(double *row, int kr, int ki, double re, d
 // and g_{j+1} = g_j exp(2 kappa N1^2): two exps per sequence and one per line
 // instead of one per mode.  The j-th factor carries about j^2 / 2 roundings
 // more than a direct exp (below 1e-14 relative for j < 8).  gauss_factors
-// writes the factor of mode k2 to f[k2].
+// hands the factor of each mode k2 to use(k2, f), so that a caller can apply
+// it at once and holds no row of factors.
 template <int N1>
 struct GaussChain {
     double kappa, step;     // log(0.9) / (c + 1)^2, exp(2 kappa N1^2)
@@ -156,8 +157,8 @@ struct GaussChain {
     }
 };
 
-template <int N1, int N2>
-__device__ __forceinline__ void gauss_factors(int q0, const GaussChain<N1> &g, double (&f)[N2])
+template <int N1, int N2, typename Use>
+__device__ __forceinline__ void gauss_factors(int q0, const GaussChain<N1> &g, Use &&use)
 {
     constexpr double inv_n = 1.0 / (N1 * N2);
     constexpr double D = N1;
@@ -169,7 +170,7 @@ __device__ __forceinline__ void gauss_factors(int q0, const GaussChain<N1> &g, d
         double ratio = exp(g.kappa * D * (2.0 * b + D));
         static_for<0, N2 / 2>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            f[h == 0 ? j : N2 - 1 - j] = fj;
+            use(std::integral_constant<int, h == 0 ? j : N2 - 1 - j>{}, fj);
             if constexpr (j + 1 < N2 / 2) {
                 fj *= ratio;
                 ratio *= g.step;
@@ -178,56 +179,140 @@ __device__ __forceinline__ void gauss_factors(int q0, const GaussChain<N1> &g, d
     });
 }
 
-// Mask of one line, with the inverse transform's 1/N folded in.  v holds
-// X[q] at q = t + N2 r + N1 k2 in v[r N2 + k2].
-//   exponential (eq. exp_filter): f = 1 for |q| <= c, else exp(-(|q| - c)).
-//     With m = floor(c), |q| <= c is |q| <= m, and above the cutoff
-//     exp(c - |q|) = exp(c - m - 1) * e^{-(|q| - m - 1)}: one exp per lane and
-//     a table of e^{-k}, instead of one exp per mode.
-//   sharp: the same with the factor above the cutoff set to 0.
-//   Gaussian (eq. gaussian_filter): f = exp(log(0.9) (|q| / (c + 1))^2),
-//     formed along the row by gauss_factors.
-template <int N1, int N2, int NV>
-__device__ __forceinline__ void apply_mask(cplx (&v)[NV], int t, int kind, double c,
-                                           const double *etab)
+// e^{n} for the offsets within the exponential mask's sequences, to 25 digits.
+constexpr double exp_int(int n)
 {
-    constexpr int N = N1 * N2;
+    return n == 0     ? 1.0
+           : n == 4   ? 5.459815003314423907811026e+1
+           : n == 8   ? 2.980957987041728274743592e+3
+           : n == -4  ? 1.831563888873418029371802e-2
+           : n == -8  ? 3.354626279025118388213891e-4
+           : n == -10 ? 4.539992976248485153559152e-5
+           : n == -12 ? 6.144212353328209758682308e-6
+           : n == -16 ? 1.125351747192591145137752e-7
+           : n == -20 ? 2.061153622438557827965940e-9
+           : n == -24 ? 3.775134544279097751644970e-11
+           : n == -30 ? 9.357622968840174604915832e-14
+           : n == -32 ? 1.266416554909417572312090e-14
+           : n == -36 ? 2.319522830243569388312264e-16
+           : n == -40 ? 4.248354255291588995329235e-18
+           : n == -48 ? 1.425164082740935106285321e-21
+           : n == -50 ? 1.928749847963917783017343e-22
+           : n == -60 ? 8.756510762696520338488733e-27
+           : n == -64 ? 1.603810890548637852976087e-28
+           : n == -70 ? 3.975449735908646807789100e-31
+           : n == -72 ? 5.380186160021138413818187e-32
+           : n == -80 ? 1.804851387845415172312128e-35
+           : n == -84 ? 3.305700626760734298455096e-37
+           : n == -96 ? 2.031092662734810925690369e-42
+           : n == -112 ? 2.285693676718671734737326e-49
+                      : __builtin_nan("");
+}
+
+// Exponential factors of one second-stage row, with the 1/N folded in, along
+// the same two sequences as gauss_factors: min(1, exp(c - |q|)) is the mask
+// (eq. exp_filter: 1 up to the cutoff, e^{-(|q| - c)} above), and the
+// exponentials of a sequence are its first member times e^{-N1 j}, so a mode
+// costs a multiplication by a constant and a minimum.  ea and eb: exp(c - t) / N and
+// exp(c - N1 + t) / N, the first members of row t's sequences (t < N2); row
+// t + N2 R takes them times e^{-+N2 R}.  c is at most N/2 (or infinite: then
+// every factor is 1/N), and c - t, c - N1 + t are exact wherever they matter:
+// a difference of two multiples of c's last place that is no larger than
+// they are.
+template <int N1, int N2, int R, typename Use>
+__device__ __forceinline__ void exp_factors(double ea, double eb, Use &&use)
+{
+    constexpr double inv_n = 1.0 / (N1 * N2);
+    static_for<0, 2>([&](auto hh) {
+        constexpr int h = decltype(hh)::value;
+        const double e = h == 0 ? ea * exp_int(-N2 * R) : eb * exp_int(N2 * R);
+        static_for<0, N2 / 2>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            use(std::integral_constant<int, h == 0 ? j : N2 - 1 - j>{}, fmin(e * exp_int(-N1 * j), inv_n));
+        });
+    });
+}
+
+// Sharp factors of one row: 1/N up to the cutoff, 0 above.
+template <int N1, int N2, typename Use>
+__device__ __forceinline__ void sharp_factors(int q0, double c, Use &&use)
+{
+    constexpr double inv_n = 1.0 / (N1 * N2);
+    static_for<0, N2>([&](auto kk) {
+        constexpr int k2 = decltype(kk)::value;
+        const int qhat = k2 < N2 / 2 ? q0 + N1 * k2 : N1 * N2 - q0 - N1 * k2;
+        use(kk, (double)qhat <= c ? inv_n : 0.0);
+    });
+}
+
+// Mask of one line, with the inverse transform's 1/N folded in.  v holds
+// X[q] at q = t + N2 r + N1 k2 in v[r N2 + k2].  The factors of a row are
+// formed by exp_factors (two exps per lane), gauss_factors (eq.
+// gaussian_filter: f = exp(log(0.9) (|q| / (c + 1))^2)) or sharp_factors.
+// The empty statement keeps each multiplication inside its branch: without it
+// the compiler sinks the multiplications behind the branches and carries a
+// factor per mode there (32 registers at N2 = 16: a workgroup that holds a
+// whole shell of 256-point lines then spilled 130).
+template <int N1, int N2, int NV>
+__device__ __forceinline__ void apply_mask(cplx (&v)[NV], int t, int kind, double c)
+{
     constexpr int R = NV / N2;
     constexpr bool PAD = NV != N1;        // padded second stage: rows k1 >= N1 are empty
-    constexpr double inv_n = 1.0 / N;
+    auto rows = [&](auto &&factors) {
+        static_for<0, R>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            if constexpr (PAD) {
+                if (t + N2 * r >= N1) return;
+            }
+            factors(rr, [&](auto kk, double f) {
+                constexpr int k2 = decltype(kk)::value;
+                cplx &x = v[r * N2 + k2];
+                x = cplx{x.re * f, x.im * f};
+                asm volatile("" : "+v"(x.re), "+v"(x.im));
+            });
+        });
+    };
     if (kind == 1) {
         const GaussChain<N1> g(c);
-        static_for<0, R>([&](auto rr) {
-            constexpr int r = decltype(rr)::value;
-            if constexpr (PAD) {
-                if (t + N2 * r >= N1) return;
-            }
-            double f[N2];
-            gauss_factors<N1, N2>(t + N2 * r, g, f);
-            static_for<0, N2>([&](auto kk) {
-                constexpr int k2 = decltype(kk)::value;
-                v[r * N2 + k2].re *= f[k2];
-                v[r * N2 + k2].im *= f[k2];
-            });
-        });
+        rows([&](auto rr, auto &&use) { gauss_factors<N1, N2>(t + N2 * decltype(rr)::value, g, use); });
+    } else if (kind == 0) {
+        constexpr double inv_n = 1.0 / (N1 * N2);
+        const double ea = exp(c - (double)t) * inv_n, eb = exp(c - (double)(N1 - t)) * inv_n;
+        rows([&](auto rr, auto &&use) { exp_factors<N1, N2, decltype(rr)::value>(ea, eb, use); });
     } else {
-        const int m = c >= (double)N ? N : (int)floor(c);
-        const double g = (kind == 0 ? exp((c - (double)m) - 1.0) : 0.0) * inv_n;
+        rows([&](auto rr, auto &&use) { sharp_factors<N1, N2>(t + N2 * decltype(rr)::value, c, use); });
+    }
+}
+
+// The same for lines that are exponential or sharp, without a branch on the
+// kind (whose phis hold registers): 1/N up to the cutoff, above it the
+// exponential or nothing.
+template <int N1, int N2, int NV>
+__device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp, double c)
+{
+    constexpr double inv_n = 1.0 / (N1 * N2);
+    constexpr int R = NV / N2;
+    constexpr bool PAD = NV != N1;
+    static_for<0, 2>([&](auto hh) {
+        constexpr int h = decltype(hh)::value;
+        // the sequences of exp_factors: |q| = b -+ N2 r + N1 j
+        const double room = c - (double)(h == 0 ? t : N1 - t);
+        const double e = sharp ? 0.0 : exp(room) * inv_n;
         static_for<0, R>([&](auto rr) {
             constexpr int r = decltype(rr)::value;
             if constexpr (PAD) {
                 if (t + N2 * r >= N1) return;
             }
-            static_for<0, N2>([&](auto kk) {
-                constexpr int k2 = decltype(kk)::value;
-                const int q = t + N2 * r + N1 * k2;
-                const int qhat = q <= N / 2 ? q : N - q;
-                const double f = qhat <= m ? inv_n : g * etab[qhat > m ? qhat - m - 1 : 0];
-                v[r * N2 + k2].re *= f;
-                v[r * N2 + k2].im *= f;
+            const double er = e * exp_int(h == 0 ? -N2 * r : N2 * r);
+            static_for<0, N2 / 2>([&](auto jj) {
+                constexpr int j = decltype(jj)::value, k2 = h == 0 ? j : N2 - 1 - j;
+                constexpr double step = (h == 0 ? N2 * r : -N2 * r) + N1 * j;
+                cplx &x = v[r * N2 + k2];
+                const double f = room >= step ? inv_n : er * exp_int(-N1 * j);
+                x = cplx{x.re * f, x.im * f};
             });
         });
-    }
+    });
 }
 
 // Ordering of LDS accesses among the lanes of one wave: lanes of a wave see
@@ -265,14 +350,13 @@ __device__ __forceinline__ void line_sync()
 // would save nothing there.)
 template <int N1, int N2, bool WAVE, int NV>
 __device__ __forceinline__ void apply_mask_pair(cplx (&v)[NV], int t, int ka, int kb, double c,
-                                                const double *etab, double *P)
+                                                double *P)
 {
     constexpr int N = N1 * N2;
     constexpr int R = NV / N2;
     constexpr bool PAD = NV != N1;
     constexpr double inv_n = 1.0 / N;
-    const int m = c >= (double)N ? N : (int)floor(c);
-    const double g_exp = exp((c - (double)m) - 1.0) * inv_n;
+    const double ea0 = exp(c - (double)t) * inv_n, eb0 = exp(c - (double)(N1 - t)) * inv_n;
     const GaussChain<N1> gc(c);
     // Each real line's kind as 0/1 weights, so that the per-mode factors are
     // blends rather than branches (a select chain on the kind was lowered to
@@ -298,19 +382,15 @@ __device__ __forceinline__ void apply_mask_pair(cplx (&v)[NV], int t, int ka, in
         if constexpr (PAD) {
             if (t + N2 * r >= N1) return;
         }
-        double fgs[N2];
-        gauss_factors<N1, N2>(t + N2 * r, gc, fgs);
+        double fgs[N2], fes[N2], fss[N2];
+        gauss_factors<N1, N2>(t + N2 * r, gc, [&](auto kk, double f) { fgs[decltype(kk)::value] = f; });
+        exp_factors<N1, N2, r>(ea0, eb0, [&](auto kk, double f) { fes[decltype(kk)::value] = f; });
+        sharp_factors<N1, N2>(t + N2 * r, c, [&](auto kk, double f) { fss[decltype(kk)::value] = f; });
         static_for<0, N2>([&](auto kk) {
             constexpr int k2 = decltype(kk)::value;
-            const double fg = fgs[k2];
             const int q = t + N2 * r + N1 * k2;
-            const int qhat = q <= N / 2 ? q : N - q;
-            const double e = etab[max(qhat - m - 1, 0)];
-            const bool below = qhat <= m;
-            const double tail = below ? inv_n : g_exp * e;     // exponential
-            const double keep = below ? inv_n : 0.0;           // sharp
-            const double fa = ga * fg + ea * tail + sa * keep;
-            const double fb = gb * fg + eb * tail + sb * keep;
+            const double fa = ga * fgs[k2] + ea * fes[k2] + sa * fss[k2];
+            const double fb = gb * fgs[k2] + eb * fes[k2] + sb * fss[k2];
             const double alpha = 0.5 * (fa + fb), beta = 0.5 * (fa - fb);
             const int qp = (N - q) % N;
             v[r * N2 + k2].re = alpha * v[r * N2 + k2].re + beta * P[qp];
@@ -424,73 +504,85 @@ __device__ __forceinline__ void twiddle_powers(cplx (&v)[NV], const Twiddle *__r
     });
 }
 
+// A zero the compiler knows nothing about; with a value: available only once
+// that value is formed.
+__device__ __forceinline__ int opaque_zero()
+{
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return zero;
+}
+__device__ __forceinline__ int opaque_zero(double after)
+{
+    int zero = 0;
+    asm volatile("" : "+v"(zero) : "v"(after));
+    return zero;
+}
+
 // Filter one complex line of length N = N1 * N2 held by N2 lanes (lane t
 // holds x[N2 n1 + t] in v[n1]); on return v holds the filtered values at the
-// same positions.  Every lane of the workgroup calls this together.
-// etab: e^{-k}, k <= N/2, in LDS, written before the first barrier here
-// (with WAVE: before a barrier of the caller's).  WAVE: the line's lanes lie
-// in one wave, so the transposes and the two-kind mask synchronise the wave
-// only, with no workgroup barrier, and `mixed` is wave-uniform.
-template <int N1, int N2, bool HYB, bool WAVE = false, int NV>
+// same positions.  Every lane of the workgroup calls this together (WAVE: of
+// the wave).  WAVE: the line's lanes lie in one wave, so the transposes and
+// the two-kind mask synchronise the wave only, with no workgroup barrier, and
+// `mixed` is wave-uniform.  tw: the table of dft_twisted, in global memory or
+// LDS.
+template <int N1, int N2, bool HYB, bool WAVE = false, bool LEAN = false,
+          bool REST = false, int NV>
 __device__ __forceinline__ void filter_line(cplx (&v)[NV], int t, int kind, int kind_b, bool mixed,
-                                            double c, double *L, const Twiddle *__restrict__ tw,
-                                            const double *etab)
+                                            double c, double *L, const Twiddle *__restrict__ tw)
 {
     // R second-stage rows per lane; when N2 does not divide N1 the last row
     // is padded (NV = R N2 > N1) and its entries k1 >= N1 are skipped
+    constexpr int N = N1 * N2;
     constexpr int R = NV / N2;
     constexpr bool PAD = NV != N1;
     static_assert(NV % N2 == 0 && NV >= N1 && NV - N1 < N2, "second stage: ceil(N1 / N2) rows");
 
-    // forward: N1-point DFTs over n1, twiddle W_N^{t k1}
+    // forward: N1-point DFTs over n1, then N2-point DFTs over n2 with the
+    // twiddles W_N^{n2 k1}: v[r N2 + k2] = X[k1 + N1 k2], k1 = t + N2 r
     dft_reg<N1, false>(v);
-    twiddle_powers<N1, false, 0>(v, tw, t);
     transpose_fwd<N1, N2, WAVE>(v, t, L);
-    // N2-point DFTs over n2: v[r N2 + k2] = X[k1 + N1 k2], k1 = t + N2 r
-    static_for<0, R>([&](auto rr) { dft_reg<N2, false, decltype(rr)::value * N2>(v); });
+    if constexpr (LEAN) tw += opaque_zero(v[0].re);
+    static_for<0, R>([&](auto rr) {
+        constexpr int r = decltype(rr)::value;
+        // a padded row's twiddles stay inside the table (its result is dropped)
+        const int k1 = t + N2 * r;
+        dft_twisted<N, N2, false, r * N2>(v, PAD && k1 >= N1 ? 0 : k1, tw);
+    });
 
     // kind: the real part's filter; kind_b: the imaginary part's.  mixed
     // (workgroup-uniform, or wave-uniform with WAVE) is set when some line of
     // the workgroup (wave) has two; only the hybrid-capable variant (HYB)
     // carries that code.
-    if constexpr (HYB) {
+    if constexpr (REST) {
+        apply_mask_two<N1, N2>(v, t, kind != 0, c);
+    } else if constexpr (HYB) {
         if (mixed)
-            apply_mask_pair<N1, N2, WAVE>(v, t, kind, kind_b, c, etab, L);
+            apply_mask_pair<N1, N2, WAVE>(v, t, kind, kind_b, c, L);
         else
-            apply_mask<N1, N2>(v, t, kind, c, etab);
+            apply_mask<N1, N2>(v, t, kind, c);
     } else {
-        apply_mask<N1, N2>(v, t, kind, c, etab);
+        apply_mask<N1, N2>(v, t, kind, c);
     }
 
-    // inverse: N2-point inverse DFTs, conjugate twiddles W_N^{-n2 k1},
-    // transpose back, N1-point inverse DFTs.  In the hybrid-capable variant
-    // the table address takes an opaque zero offset here, so that the
-    // inverse twiddles are not loaded before the two-kind mask and held
-    // across it (that pushed the register count past the two-wave limit and
-    // spilled 16-40 registers at N = 256).
-    const Twiddle *tw_inv = tw;
-    if constexpr (HYB) {
-        int zero = 0;
-        asm volatile("" : "+v"(zero));
-        tw_inv = tw + zero;
+    // inverse: N2-point inverse DFTs, transpose back, N1-point inverse DFTs
+    // with the conjugate twiddles W_N^{-n2 k1} (multiplied beforehand where
+    // N1 has a factor 3 or 5).  The table address takes an opaque zero offset
+    // here, so that the inverse twiddles are not loaded early and held.
+    const int zero = LEAN ? opaque_zero(v[0].re) : opaque_zero();
+    const Twiddle *tw_inv = tw + zero;
+    if constexpr (LEAN) {
+        t += zero;
+        L += zero;
     }
-    static_for<0, R>([&](auto rr) {
-        constexpr int r = decltype(rr)::value;
-        dft_reg<N2, true, r * N2>(v);
-        // a padded row's twiddles stay inside the table (its result is dropped)
-        const int k1 = t + N2 * r;
-        twiddle_powers<N2, true, r * N2>(v, tw_inv, PAD && k1 >= N1 ? 0 : k1);
-    });
+    static_for<0, R>([&](auto rr) { dft_reg<N2, true, decltype(rr)::value * N2>(v); });
     transpose_bwd<N1, N2, WAVE>(v, t, L);
-    dft_reg<N1, true>(v);
-}
-
-// Copy e^{-k}, k in [0, N/2], into the workgroup's LDS table.
-template <int N>
-__device__ __forceinline__ void stage_exp_table(double *etab, const double *__restrict__ eneg,
-                                                int lane)
-{
-    for (int i = lane; i <= N / 2; i += (int)blockDim.x) etab[i] = eneg[i];
+    if constexpr ((N1 & (N1 - 1)) == 0) {
+        dft_twisted<N, N1, true>(v, t, tw_inv);
+    } else {
+        twiddle_powers<N1, true, 0>(v, tw_inv, t);
+        dft_reg<N1, true>(v);
+    }
 }
 
 // N = N1 * N2: N2 lanes per line, N1 values per lane.  After the transpose
@@ -698,9 +790,7 @@ template <int N, int C, bool HYB>
 __device__ __forceinline__ void theta_block(const double *in, double *out,
                                             const ThetaItem *__restrict__ items, int n_valid,
                                             int cp_log2, int tile, int n_theta, int n_phi,
-                                            const Twiddle *__restrict__ tw,
-                                            const double *__restrict__ eneg, double *lds,
-                                            double *etab, int *flags, const HybridArgs &h, int lane)
+                                            const Twiddle *__restrict__ tw, double *lds, int *flags, const HybridArgs &h, int lane)
 {
     constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
     static_assert(C * N2 == 256 || C * N2 == 128, "theta workgroups have 256 or 128 lanes");
@@ -711,7 +801,6 @@ __device__ __forceinline__ void theta_block(const double *in, double *out,
     if (valid) it = items[u];
     const bool active = valid && !(it.flags & kFlagIdentity);
     const int any_active = __syncthreads_or(active);
-    if (any_active) stage_exp_table<N>(etab, eneg, lane);
 
     const size_t base = (size_t)it.shell * (size_t)(n_theta * n_phi);
     const int half = n_phi / 2;
@@ -752,7 +841,7 @@ __device__ __forceinline__ void theta_block(const double *in, double *out,
         if constexpr (HYB)
             hybrid_kinds<N1, N2, false>(v, t, L, flags, p, C, active, ka, dline + kr, dline + ki, h,
                                         &ka, &kb, &mixed);
-        filter_line<N1, N2, HYB>(v, t, ka, kb, mixed, active ? it.c : INFINITY, L, tw, etab);
+        filter_line<N1, N2, HYB>(v, t, ka, kb, mixed, active ? it.c : INFINITY, L, tw);
     }
     if (valid && (active || !any_active)) {
         static_for<0, N1>([&](auto nn) {
@@ -781,16 +870,17 @@ __device__ __forceinline__ void theta_block(const double *in, double *out,
 // (p, t) with t fastest): line p packs ring items[p].ring (real part) and its
 // mirror ring n_theta-1-j of the same shell (imaginary part), which shares
 // m_max.  Lines p >= n_valid are idle.  A line's N2 lanes are consecutive
-// lanes of one wave, so the line filter synchronises per wave; the worker
-// itself takes three workgroup barriers (the any-active vote, the staged
-// e^{-k} table, the end).  All lanes call this together.
+// lanes of one wave, so everything here synchronises per wave, with no
+// workgroup barrier: a caller that runs another worker next on the same LDS
+// puts one in between.  All lanes call this together.  REST: rings of shells
+// that the theta pass leaves alone, which are exponential or sharp (a Gaussian
+// or hybrid shell is never left alone): the Gaussian's code and registers are
+// left out, and the line filter holds as few registers as it can.
 // ---------------------------------------------------------------------------
-template <int N, int LINES, bool HYB>
+template <int N, int LINES, bool HYB, bool REST = false>
 __device__ __forceinline__ void phi_block(const double *in, double *out,
                                           const PhiItem *__restrict__ items, int n_valid,
-                                          int n_theta, const Twiddle *__restrict__ tw,
-                                          const double *__restrict__ eneg, double *lds,
-                                          double *etab, int *flags, const HybridArgs &h, int lane)
+                                          int n_theta, const Twiddle *__restrict__ tw, double *lds, int *flags, const HybridArgs &h, int lane)
 {
     constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
     const int t = lane % N2, p = lane / N2;
@@ -798,8 +888,7 @@ __device__ __forceinline__ void phi_block(const double *in, double *out,
     PhiItem it{0, kFlagIdentity, 0.0};
     if (valid) it = items[p];
     const bool active = valid && !(it.flags & kFlagIdentity);
-    const int any_active = __syncthreads_or(active);
-    if (any_active) stage_exp_table<N>(etab, eneg, lane);
+    const bool any_active = __any(active);          // of the wave's lines
 
     const int j = it.ring % n_theta;
     const size_t a = (size_t)it.ring * N;
@@ -812,17 +901,14 @@ __device__ __forceinline__ void phi_block(const double *in, double *out,
                       : cplx{0.0, 0.0};
     });
     if (any_active) {
-        // the line filter synchronises each line's wave only: the e^{-k}
-        // table staged above needs this one workgroup barrier
-        __syncthreads();
         double *L = lds + p * line_stride<N1, N2, HYB>();
         const size_t ring_b = (size_t)it.ring + (size_t)(n_theta - 1 - 2 * j);
-        int ka = it.flags & kKindMask, kb = ka;
+        int ka = it.flags & (REST ? 2 : kKindMask), kb = ka;
         bool mixed = false;
         if constexpr (HYB)
             hybrid_kinds<N1, N2, true>(v, t, L, flags, p, LINES, active, ka, (size_t)it.ring, ring_b,
                                        h, &ka, &kb, &mixed);
-        filter_line<N1, N2, HYB, true>(v, t, ka, kb, mixed, active ? it.c : INFINITY, L, tw, etab);
+        filter_line<N1, N2, HYB, true, REST, REST>(v, t, ka, kb, mixed, active ? it.c : INFINITY, L, tw);
     }
     if (valid && (active || !any_active)) {
         static_for<0, N1>([&](auto nn) {
@@ -837,9 +923,6 @@ __device__ __forceinline__ void phi_block(const double *in, double *out,
             st_stream<ring_stores_streamed<N>()>(out + b + N2 * n1 + t, ld_stream(in + b + N2 * n1 + t));
         });
     }
-    // a caller that runs another worker next (the batch kernels) must not
-    // overwrite the LDS before every wave is done with its lines
-    __syncthreads();
 }
 
 }  // namespace sphfilt
@@ -1008,9 +1091,7 @@ template <int N, bool ADJ, bool HYB, bool MFMA = false, int W = 256>
 __device__ __forceinline__ void shell_block(const double *in, double *out,
                                             const ThetaItem *__restrict__ items,
                                             const double *__restrict__ ring_c, int n_valid,
-                                            const Twiddle *__restrict__ tw,
-                                            const double *__restrict__ eneg, double *lds,
-                                            double *etab, int *flags, const HybridArgs &ht,
+                                            const Twiddle *__restrict__ tw, double *lds, int *flags, const HybridArgs &ht,
                                             const HybridArgs &hp, int lane, double *gaux = nullptr)
 {
     static_assert(!MFMA || (!HYB && (N == 32 || N == 64)), "circulant theta: plain kinds, N = 32, 64");
@@ -1018,8 +1099,6 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
     using S = ShellShape<N, W>;
     constexpr int N1 = S::N1, N2 = S::N2, C = W / N2;
     constexpr size_t shell_pts = (size_t)N * N / 2;
-    stage_exp_table<N>(etab, eneg, lane);
-
     // The theta side of the shell moves straight between HBM and registers in
     // the theta layout (row segments, as the theta kernel does).  At N = 128
     // the phi side does too, in the phi layout (ring pieces of 64 bytes, as
@@ -1069,7 +1148,7 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
             hybrid_kinds<N1, N2, false>(v, tt, L, flags, pt, C, valid_t, ka, dline + kr,
                                  dline + kr + S::lines, ht, &ka, &kb, &mixed);
         }
-        filter_line<N1, N2, HYB>(v, tt, ka, kb, mixed, valid_t ? it.c : INFINITY, L, tw, etab);
+        filter_line<N1, N2, HYB>(v, tt, ka, kb, mixed, valid_t ? it.c : INFINITY, L, tw);
     };
     auto phi_filter = [&]() {
         double *L = lds + pp * line_stride<N1, N2, HYB>();
@@ -1080,7 +1159,7 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
             hybrid_kinds<N1, N2, true>(v, tp, L, flags, pp, C, valid_p, ka, ring,
                                  ring + (size_t)(N / 2 - 1 - 2 * j), hp, &ka, &kb, &mixed);
         }
-        filter_line<N1, N2, HYB, true>(v, tp, ka, kb, mixed, c_p, L, tw, etab);
+        filter_line<N1, N2, HYB, true>(v, tp, ka, kb, mixed, c_p, L, tw);
         // the phi line filter synchronises each line's wave only; its LDS
         // scratch overlaps the staging area and other lines' scratch
         __syncthreads();
@@ -1092,7 +1171,7 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
         if constexpr (MFMA) {
             constexpr int K = N / 2, SH = S::shells;
             double *fq = gaux, *cosd = gaux + SH * (N / 2 + 1), *cvec = cosd + N;
-            shell_circulants<N, SH>(items, n_valid, tw, etab, fq, cosd, cvec, lane);
+            shell_circulants<N, SH>(items, n_valid, tw, fq, cosd, cvec, lane);
             dv4 acc[gemm_tiles_per_wave<N, SH>()];
             auto sign = [&](int sh) { return (items[sh].flags & kFlagOddParity) ? -1.0 : 1.0; };
             shell_gemm<N, SH>(cvec, n_valid, lane, acc, [&](int sh, int m, int k, bool first) {
@@ -1134,7 +1213,6 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
     } else {
         if constexpr (phi_direct) {
             shell_phi_hbm<N, true>(in, out, base_p, v, tp, j, valid_p);
-            __syncthreads();                    // the e^{-k} table staged above
         } else {
             shell_phi_io<N, false, W>(v, sb_p, tp, j);
             __syncthreads();

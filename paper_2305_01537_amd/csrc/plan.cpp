@@ -39,7 +39,6 @@ struct DeviceTables {
     PhiItem *phi = nullptr;
     Twiddle *tw_theta = nullptr;
     Twiddle *tw_phi = nullptr;
-    double *eneg = nullptr;
     double *fused_c = nullptr;
     PhiItem *phi_rest = nullptr;
     PhiItem *phi_in = nullptr;
@@ -83,7 +82,6 @@ void free_device(DeviceTables *d)
     if (d->phi) (void)hipFree(d->phi);
     if (d->tw_theta) (void)hipFree(d->tw_theta);
     if (d->tw_phi) (void)hipFree(d->tw_phi);
-    if (d->eneg) (void)hipFree(d->eneg);
     if (d->fused_c) (void)hipFree(d->fused_c);
     if (d->phi_rest) (void)hipFree(d->phi_rest);
     if (d->phi_in) (void)hipFree(d->phi_in);
@@ -122,18 +120,18 @@ hipError_t theta_split(sphfilt_plan p, const double *in, double *out, const Thet
     hipError_t e = hipSuccess;
     if (nh > 0)
         e = launch_theta(2 * p->n_theta, p->theta_cols, in, out, items, nh, p->n_theta, p->n_phi,
-                         p->dev.tw_theta, p->dev.eneg, pass_args(p, d.theta, d, true), s);
+                         p->dev.tw_theta, pass_args(p, d.theta, d, true), s);
     int done = nh;
     if (p->theta_mfma && e == hipSuccess) {
         const int na = n < p->host.theta_active ? n : p->host.theta_active;
         if (na > nh)
             e = launch_theta_gemm(p->n_theta, p->n_phi, in, out, items + nh, na - nh,
-                                  p->dev.tw_theta, p->dev.eneg, s);
+                                  p->dev.tw_theta, s);
         done = na > nh ? na : nh;
     }
     if (e == hipSuccess && n > done)
         e = launch_theta(2 * p->n_theta, p->theta_cols, in, out, items + done, n - done, p->n_theta,
-                         p->n_phi, p->dev.tw_theta, p->dev.eneg, pass_args(p, d.theta, d, false), s);
+                         p->n_phi, p->dev.tw_theta, pass_args(p, d.theta, d, false), s);
     return e;
 }
 
@@ -143,11 +141,10 @@ hipError_t phi_split(sphfilt_plan p, const double *in, double *out, const PhiIte
     const int nh = n_hyb < n ? n_hyb : n;
     hipError_t e = hipSuccess;
     if (nh > 0)
-        e = launch_phi(p->n_phi, p->phi_lines, in, out, items, nh, p->n_theta, p->dev.tw_phi,
-                       p->dev.eneg, pass_args(p, d.phi, d, true), s);
+        e = launch_phi(p->n_phi, p->phi_lines, in, out, items, nh, p->n_theta, p->dev.tw_phi, pass_args(p, d.phi, d, true), s);
     if (e == hipSuccess && n > nh)
         e = launch_phi(p->n_phi, p->phi_lines, in, out, items + nh, n - nh, p->n_theta,
-                       p->dev.tw_phi, p->dev.eneg, pass_args(p, d.phi, d, false), s);
+                       p->dev.tw_phi, pass_args(p, d.phi, d, false), s);
     return e;
 }
 
@@ -194,12 +191,12 @@ int apply_fused(sphfilt_plan p, bool adjoint, const double *in, double *out, con
     // rings of the theta-idle shells (never hybrid) with the plain one
     if (nh > 0)
         e = launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta, p->dev.fused_c,
-                             nh, p->dev.phi_rest, 0, p->dev.tw_phi, p->dev.eneg,
+                             nh, p->dev.phi_rest, 0, p->dev.tw_phi,
                              pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
     if (e == hipSuccess && (t.n_fused > nh || n_rings > 0))
         e = launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta + nh,
                              p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh, p->dev.phi_rest,
-                             n_rings, p->dev.tw_phi, p->dev.eneg, pass_args(p, d.theta, d, false),
+                             n_rings, p->dev.tw_phi, pass_args(p, d.theta, d, false),
                              pass_args(p, d.phi, d, false), s, p->theta_mfma != 0);
     return e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
 }
@@ -266,7 +263,7 @@ int apply_overlap(sphfilt_plan p, bool adjoint, double *x, const Decisions &d, h
     // the rings of theta-idle shells: never hybrid
     if (e == hipSuccess)
         e = launch_phi(p->n_phi, p->phi_lines, x, x, p->dev.phi_rest, t.phi_rest_active,
-                       p->n_theta, p->dev.tw_phi, p->dev.eneg, pass_args(p, d.phi, d, false), side);
+                       p->n_theta, p->dev.tw_phi, pass_args(p, d.phi, d, false), side);
     if (e == hipSuccess) e = adjoint ? theta() : rings_in();
     if (e == hipSuccess) e = hipEventRecord(p->side.join, side);
     if (e == hipSuccess) e = hipStreamWaitEvent(s, p->side.join, 0);
@@ -605,7 +602,6 @@ int sphfilt_plan_create(sphfilt_plan *out, int n_r, int n_theta, int n_phi, int 
         if (!rc) rc = upload(&p->dev.phi, p->host.phi);
         if (!rc) rc = upload(&p->dev.tw_theta, twiddles(2 * n_theta));
         if (!rc) rc = upload(&p->dev.tw_phi, twiddles(n_phi));
-        if (!rc) rc = upload(&p->dev.eneg, exp_table());
         if (!rc) rc = upload(&p->dev.fused_c, p->host.fused_c);
         if (!rc) rc = upload(&p->dev.phi_rest, p->host.phi_rest);
         if (!rc) rc = upload(&p->dev.phi_in, p->host.phi_in);

@@ -41,24 +41,20 @@ struct HybridArgs {
     int present;
 };
 
-// Length of the e^{-k} table: covers k <= N/2 for every supported N.
-constexpr int kExpTable = 512;
-
 struct Twiddle {
-    double re, im;         // exp(-2 pi i j / N)
+    double re, im;         // exp(-2 pi i j / N), or cos and tan of 2 pi j / N
 };
 
 // Launchers (kernels_theta.hip, kernels_phi.hip, kernels.hip).  All return
 // hipSuccess or the launch error.
 // theta: n_items shells, each split in tiles of 2*cols meridian columns.
-// eneg: e^{-k} for k in [0, kExpTable), used by the exponential mask.
 hipError_t launch_theta(int n_line, int cols, const double *in, double *out,
                         const ThetaItem *items, int n_items, int n_theta, int n_phi,
-                        const Twiddle *tw, const double *eneg, const HybridArgs &h,
+                        const Twiddle *tw, const HybridArgs &h,
                         hipStream_t stream);
 // phi: n_items ring pairs, `lines` of them per workgroup.
 hipError_t launch_phi(int n_line, int lines, const double *in, double *out, const PhiItem *items,
-                      int n_items, int n_theta, const Twiddle *tw, const double *eneg,
+                      int n_items, int n_theta, const Twiddle *tw,
                       const HybridArgs &h, hipStream_t stream);
 
 // Fused shells: both passes of n_shells shells (every line of which is
@@ -72,16 +68,14 @@ hipError_t launch_phi(int n_line, int lines, const double *in, double *out, cons
 // needs theta_gemm_ok; a launch with hybrid shells must pass false).
 hipError_t launch_shell_phi(bool adjoint, int n_theta, int n_phi, const double *in, double *out,
                             const ThetaItem *shells, const double *ring_c, int n_shells,
-                            const PhiItem *rings, int n_rings, const Twiddle *tw,
-                            const double *eneg, const HybridArgs &ht, const HybridArgs &hp,
+                            const PhiItem *rings, int n_rings, const Twiddle *tw, const HybridArgs &ht, const HybridArgs &hp,
                             hipStream_t stream, bool mfma = false);
 // The theta pass as the circulant product on the matrix cores, over active
 // shells of plain kinds, on grids with theta_gemm_ok (n_phi = 2 n_theta in
 // {32, 64}); tw: the twiddle table of length n_phi.
 bool theta_gemm_ok(int n_theta, int n_phi);
 hipError_t launch_theta_gemm(int n_theta, int n_phi, const double *in, double *out,
-                             const ThetaItem *items, int n_items, const Twiddle *tw,
-                             const double *eneg, hipStream_t stream);
+                             const ThetaItem *items, int n_items, const Twiddle *tw, hipStream_t stream);
 // n_phi = 2 n_theta in {32, 64, 128}: whole shells per 256-lane workgroup.
 bool shell_fusable(int n_theta, int n_phi);
 int shells_per_group(int n_phi);

@@ -43,34 +43,32 @@ struct GemmShape {
 };
 
 // Mask factor f(|q|; c) of one mode, without the 1/N (kinds as in
-// apply_mask: 0 exponential, 1 Gaussian, 2 sharp; etab holds e^{-k}).
+// apply_mask: 0 exponential, 1 Gaussian, 2 sharp).
 template <int N>
-__device__ __forceinline__ double mask_factor(int kind, int qhat, double c, const double *etab)
+__device__ __forceinline__ double mask_factor(int kind, int qhat, double c)
 {
     if (kind == 1) {
         const double u = (double)qhat / (c + 1.0);
         return exp(-0.10536051565782630123 * u * u);
     }
-    const int m = c >= (double)N ? N : (int)floor(c);
-    if (qhat <= m) return 1.0;
-    return kind == 0 ? exp((c - (double)m) - 1.0) * etab[qhat - m - 1] : 0.0;
+    if ((double)qhat <= c) return 1.0;
+    return kind == 0 ? exp(c - (double)qhat) : 0.0;
 }
 
 // Circulants of the workgroup's S shells (items[0, n_valid)) into
 // cvec[S][N]: first the N/2 + 1 distinct mask factors of each shell into
 // fq[S][N/2 + 1], then c[d] from them with the cosine table cosd[j] =
 // cos(2 pi j / N) = tw[j].re.  All lanes call this together; it ends with a
-// barrier.  The caller staged etab (e^{-k}, k <= N/2) before a barrier.
+// barrier.
 template <int N, int S>
 __device__ __forceinline__ void shell_circulants(const ThetaItem *__restrict__ items, int n_valid,
-                                                 const Twiddle *__restrict__ tw,
-                                                 const double *etab, double *fq, double *cosd,
+                                                 const Twiddle *__restrict__ tw, double *fq, double *cosd,
                                                  double *cvec, int lane)
 {
     constexpr int H = N / 2 + 1;
     for (int i = lane; i < S * H; i += (int)blockDim.x) {
         const int s = i / H, q = i % H;
-        fq[i] = s < n_valid ? mask_factor<N>(items[s].flags & kKindMask, q, items[s].c, etab) : 0.0;
+        fq[i] = s < n_valid ? mask_factor<N>(items[s].flags & kKindMask, q, items[s].c) : 0.0;
     }
     for (int j = lane; j < N; j += (int)blockDim.x) cosd[j] = tw[j].re;
     __syncthreads();
