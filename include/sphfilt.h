@@ -152,7 +152,8 @@ int sphfilt_plan_destroy(sphfilt_plan plan);
  *            all ones are not touched.  Any other overlap of the two ranges is
  *            SPHFILT_EINVAL.
  *   stream   a hipStream_t (NULL = the null stream).
- * Enqueues two kernels and returns; SPHFILT_EDEVICE if a launch fails.
+ * Enqueues one kernel or a few (see sphfilt_plan_set_fused) and returns;
+ * SPHFILT_EDEVICE if a launch fails.
  */
 int sphfilt_apply(sphfilt_plan plan, const double *in, double *out, void *stream);
 
@@ -233,6 +234,12 @@ int sphfilt_plan_get_schedule(sphfilt_plan plan, int *theta_cols, int *phi_lines
  * rounding (the same line transforms, with multiply-adds contracted
  * differently by the compiler).
  *   enable  1 (the default): fuse where possible; 0: always two passes.
+ * The same setting covers joined shells: on grids with n_phi = 2 * n_theta in
+ * {48, 80, 96, 160, 192, 256} a shell of a plain kind that the theta pass
+ * filters is held in the registers of one workgroup for both passes (at 160,
+ * 192 and 256 only as many as fill rounds of one shell per compute unit, see
+ * kernels_join.hip; hybrid shells take two passes).  Joined shells are not
+ * counted in shells_fused and bytes_fused_inplace.
  * set_fused returns SPHFILT_EINVAL for other values; it is not thread-safe
  * against concurrent apply calls on the same plan.  get_fused reports the
  * setting and the number of shells fused when it is on (NULL outputs are

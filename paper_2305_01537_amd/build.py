@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(ROOT, "_build", "sphfilt")
 LIB = os.path.join(HERE, "libsphfilt.so")
 SOURCES = ["host_tables.cpp", "tune_cache.cpp", "plan.cpp", "batch.cpp", "kernels.hip", "kernels_theta.hip",
-           "kernels_phi.hip", "batch.hip", "batch_plain.hip", "batch_hybrid.hip",
+           "kernels_phi.hip", "kernels_join.hip", "batch.hip", "batch_plain.hip", "batch_hybrid.hip",
            "batch_mixed.hip", "batch_mixed_hybrid.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -37,7 +37,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # The plan kernels have no such loops and are built unchanged.
 PER_SOURCE_FLAGS = {s: ["-mllvm", "-disable-machine-licm"]
                     for s in ("batch_plain.hip", "batch_hybrid.hip", "batch_mixed.hip",
-                              "batch_mixed_hybrid.hip")}
+                              "batch_mixed_hybrid.hip", "kernels_join.hip")}
 
 
 def _jobs() -> int:

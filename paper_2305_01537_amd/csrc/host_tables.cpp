@@ -102,6 +102,7 @@ void build_items(int n_r, int n_theta, int n_phi, int n_fields, const int *parit
                  const sphfilt_cutoff *cut, HostTables *h)
 {
     const bool fusable = shell_fusable(n_theta, n_phi);
+    bool joinable = !fusable && join_supported(n_theta, n_phi);
     std::vector<ThetaItem> tf, ta, ti;     // fused, other active, identity shells
     std::vector<PhiItem> pa, pi, ra, ri;   // all rings; rings of unfused shells
     std::vector<PhiItem> rings;
@@ -141,6 +142,11 @@ void build_items(int n_r, int n_theta, int n_phi, int n_fields, const int *parit
                 for (const PhiItem &p : rings) h->fused_c.push_back(p.c);
             } else {
                 (ident ? ti : ta).push_back(t);
+                if (!ident) {
+                    joinable = joinable && all_rings;
+                    if (joinable)
+                        for (const PhiItem &p : rings) h->join_c.push_back(p.c);
+                }
                 if (ident)
                     for (const PhiItem &p : rings) ((p.flags & kFlagIdentity) ? ri : ra).push_back(p);
                 else
@@ -149,6 +155,7 @@ void build_items(int n_r, int n_theta, int n_phi, int n_fields, const int *parit
             }
         }
     }
+    if (!joinable) h->join_c.clear();
     h->n_fused = (int)tf.size();
     h->theta_active = (int)(tf.size() + ta.size());
     h->phi_active = (int)pa.size();

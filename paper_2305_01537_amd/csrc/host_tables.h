@@ -22,6 +22,10 @@ struct HostTables {
     int phi_active = 0;
     int n_fused = 0;
     std::vector<double> fused_c;
+    // Joined shells (join_supported grids that are not fusable): the ring-pair
+    // cutoffs of the active shells, in the order of theta; empty unless every
+    // active shell has all its rings filtered.
+    std::vector<double> join_c;
     std::vector<PhiItem> phi_rest;
     int phi_rest_active = 0;
     std::vector<PhiItem> phi_in;

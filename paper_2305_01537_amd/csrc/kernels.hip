@@ -190,6 +190,13 @@ static hipError_t shell_phi_go(bool adjoint, const double *in, double *out,
                                hipStream_t s)
 {
     const bool hyb = ht.present != 0;
+    if constexpr (N == 128) {           // plain shells of this size are joined (kernels_join.hip)
+        if (!hyb) return hipErrorInvalidValue;
+        return adjoint ? shell_phi_launch<N, true, true, false>(in, out, shells, ring_c, n_shells, rings,
+                                                                n_rings, tw, ht, hp, s)
+                       : shell_phi_launch<N, false, true, false>(in, out, shells, ring_c, n_shells, rings,
+                                                                 n_rings, tw, ht, hp, s);
+    }
 #define SPHFILT_SHELL_PHI(A, H)                                                                    \
     return shell_phi_launch<N, A, H, MFMA && !H>(in, out, shells, ring_c, n_shells, rings, n_rings, \
                                                  tw, ht, hp, s)

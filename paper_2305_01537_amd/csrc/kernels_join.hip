@@ -1,0 +1,143 @@
+// kernels_join.hip -- per-plan kernels that run both passes of whole shells in
+// registers (shell_join.h), double FFT filter (arXiv:2305.01537, Sec. II.A)
+// for gfx950, FP64.
+#include "shell_join.h"
+
+namespace sphfilt {
+
+// Waves per SIMD asked for, as many as the workgroups that fit a compute
+// unit's LDS hold: the register cap is 512 / waves.
+template <int N>
+constexpr int join_waves()
+{
+    return N == 256 || N == 128 ? 4 : 3;
+}
+
+// Shells and, in the same grid, ring pairs of other shells (as many as a
+// workgroup's lanes hold).  What bounds it: at 256 points a workgroup is a
+// whole compute unit, 25 us of which half is FP64 issue (1,600 instructions
+// per wave and pass, 40 % of the issue slots), a quarter waits for the load and
+// the store, and the LDS is busy for a third; nothing else runs on the unit
+// meanwhile.  Against two passes, whose bound is HBM: 24 x 256 shells of
+// 128 x 256, all filtered, 1087 -> 820 us forward (3.9 TB/s of 16 B per point),
+// 1090 -> 855 adjoint; at cal-L = 3, 187 -> 157.  Shorter lines fit two to six
+// workgroups per unit and come near the bandwidth: all filtered, 24 x 3600
+// shells of 24 x 48 754 -> 355 us, 24 x 1300 of 40 x 80 725 -> 503, 24 x 900 of
+// 48 x 96 573 -> 345, 24 x 508 of 64 x 128 413 -> 325 (in LDS), 24 x 160 of 80 x
+// 160 308 -> 260, 24 x 128 of 96 x 192 330 -> 265.
+template <int N, bool ADJ>
+__global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N>())))
+void join_kernel(const double *in, double *out, const ThetaItem *__restrict__ shells,
+                 const double *__restrict__ ring_c, int n_shells, int shell_groups, int span,
+                 const PhiItem *__restrict__ rings, int n_rings, const Twiddle *__restrict__ tw)
+{
+    using S = JoinShape<N>;
+    __shared__ double lds[S::lds];
+    __shared__ Twiddle table[S::table];
+    // the shell groups are spread evenly over the first `span` workgroups
+    const int b = blockIdx.x;
+    const int group = b < span ? (int)((long long)b * shell_groups / span) : shell_groups;
+    const bool ring = b >= span || (int)((long long)(b + 1) * shell_groups / span) == group;
+    if (ring) {
+        constexpr int LINES = S::width / S::N2;
+        const int first = (b - group) * LINES;
+        phi_block<N, LINES, false, true>(in, out, rings + first, min(LINES, n_rings - first), N / 2, tw, lds,
+                                         nullptr, HybridArgs{}, threadIdx.x);
+        return;
+    }
+    for (int i = threadIdx.x; i < S::table; i += S::width) table[i] = tw[i];
+    const int first = group * S::shells;
+    const int n_valid = min(S::shells, n_shells - first);
+    auto run = [&](auto kind) {
+        join_block<N, ADJ, decltype(kind)::value>(in, out, shells + first,
+                                                  ring_c + (size_t)first * S::lines, n_valid, table, lds);
+    };
+    if constexpr (S::shells > 1) {
+        run(std::integral_constant<int, -1>{});
+    } else {
+        // one shell per workgroup: one kind, and no registers held across the
+        // branches between the kinds' masks
+        const int kind = shells[first].flags & kKindMask;
+        if (kind == 0) run(std::integral_constant<int, 0>{});
+        else if (kind == 1) run(std::integral_constant<int, 1>{});
+        else run(std::integral_constant<int, 2>{});
+    }
+}
+
+template <int N>
+static hipError_t join_go(bool adjoint, const double *in, double *out, const ThetaItem *shells,
+                          const double *ring_c, int n_shells, const PhiItem *rings, int n_rings,
+                          bool spread, const Twiddle *tw, hipStream_t s)
+{
+    using S = JoinShape<N>;
+    constexpr int LINES = S::width / S::N2;
+    const int groups = (n_shells + S::shells - 1) / S::shells;
+    const int ring_groups = (n_rings + LINES - 1) / LINES;
+    const dim3 grid((unsigned)(groups + ring_groups)), block(S::width);
+    const int span = groups + (spread ? ring_groups * 4 / 5 : 0);
+    if (adjoint)
+        join_kernel<N, true><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, rings, n_rings, tw);
+    else
+        join_kernel<N, false><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, rings, n_rings, tw);
+    return hipGetLastError();
+}
+
+bool join_supported(int n_theta, int n_phi)
+{
+    return n_phi == 2 * n_theta && (n_phi == 48 || n_phi == 80 || n_phi == 96 || n_phi == 160 ||
+                                    n_phi == 192 || n_phi == 256);
+}
+
+// Lines of 160 points and more: one workgroup fills a compute unit, so a launch
+// runs in rounds of one shell per unit, and a last round that leaves most units
+// idle costs as much as a full one, where two passes spread few shells over
+// all units.  Two passes against a round, us, for 96 / 128 / 192 shells: 24.8 /
+// 28.4 / 37.4 against 30.0 / 30.6 / 34.0 at 256 points, 18.7 / 20.1 / 26.4
+// against 21.0 / 21.2 / 22.0 at 192, 16.1 / 17.6 / 19.8 against 17.4 / 17.9 /
+// 18.6 at 160: the line lies at 9/16 of the units.  Where the ring pairs of
+// other shells fill the units by themselves (join_spread) no round is short.
+// Shorter lines fit several workgroups per unit and are joined always (96
+// points, 4 shells: 8.7 against 10.8 us).
+int join_count(int n_line, int n, int n_rings, int compute_units)
+{
+    if (n_line < 160 || compute_units <= 0 || join_spread(n_line, n_rings, compute_units)) return n;
+    const int last = n % compute_units;
+    return 16 * last < 9 * compute_units ? n - last : n;
+}
+
+// Whether to spread the shells among the ring workgroups of their launch (the
+// first 4/5 of them) instead of putting them first.  A unit that holds a shell
+// computes for most of its time while the ring workgroups wait for memory, so
+// spread shells overlap the two; but they also start later, which pays only
+// where the rings run for several rounds: from two full rounds on (24 x 256
+// shells of 128 x 256 at cal-L = 3, 3.4 rounds: 157 us spread, 176 shells
+// first, 166 as two launches; 24 x 128 of 96 x 192 at cal-L = 2, 2.6 rounds:
+// 88 / 93 / 102; 24 x 160 of 80 x 160 at cal-L = 4, 1.7 rounds: 43 / 40 / 42).
+bool join_spread(int n_line, int n_rings, int compute_units)
+{
+    const int lines = n_line == 256 ? JoinShape<256>::width / JoinShape<256>::N2
+                      : n_line == 192 ? JoinShape<192>::width / JoinShape<192>::N2
+                      : n_line == 160 ? JoinShape<160>::width / JoinShape<160>::N2
+                                      : 0;
+    return lines > 0 && n_rings >= 2 * compute_units * lines;
+}
+
+hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
+                       const ThetaItem *shells, const double *ring_c, int n_shells,
+                       const PhiItem *rings, int n_rings, bool spread, const Twiddle *tw, hipStream_t s)
+{
+    if (n_shells < 0 || n_rings < 0) return hipErrorInvalidValue;
+    if (n_shells + n_rings == 0) return hipSuccess;
+    switch (n_line) {
+    case 48: return join_go<48>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 80: return join_go<80>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 96: return join_go<96>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 128: return join_go<128>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 160: return join_go<160>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 192: return join_go<192>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 256: return join_go<256>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace sphfilt

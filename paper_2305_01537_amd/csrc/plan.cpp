@@ -10,9 +10,10 @@
 // sharp filters) are sorted after the others: an in-place call launches over
 // the non-identity prefix only, an out-of-place call over all items and the
 // identity ones are copied.
-// On grids whose shells fit in LDS (n_phi = 2 n_theta in {32, 64, 128}), shells with no
-// identity line are run by the fused shell kernel (both passes, one HBM round
-// trip), in one launch with the ring pairs of the remaining shells.
+// On grids with n_phi = 2 n_theta, shells with no identity line are run by a
+// kernel that does both passes with one HBM round trip, in one launch with the
+// ring pairs of the remaining shells: the fused shell kernel (through LDS) at
+// n_phi = 32 and 64, the joined shell kernel (in registers) elsewhere.
 #include "../../include/sphfilt.h"
 #include "host_tables.h"
 #include "sphfilt_internal.h"
@@ -40,8 +41,9 @@ struct DeviceTables {
     Twiddle *tw_theta = nullptr;
     Twiddle *tw_phi = nullptr;
     double *fused_c = nullptr;
-    PhiItem *phi_rest = nullptr;
-    PhiItem *phi_in = nullptr;
+    double *join_c = nullptr;
+    PhiItem *phi_in = nullptr;       // phi_in, then phi_rest
+    PhiItem *phi_rest = nullptr;     // in the same allocation
 };
 
 // A second stream of the plan, for ring pairs that do not depend on the theta
@@ -69,6 +71,8 @@ struct sphfilt_plan_s {
     int theta_mfma;         // theta pass as the circulant product on the matrix cores
     int overlap;            // 0 off, 1 auto, 2 always: independent rings on the side stream
     HybridArgs hybrid;      // detector parameters; dec / replay set per call
+    int compute_units;
+    int n_join;             // joined shells: theta items [theta_hyb, theta_hyb + n_join)
     SideStream side;
     uint64_t params_hash;   // grid, fields and cutoffs (the tune cache key, with the GPU arch)
     double tuned_us, default_us;
@@ -83,7 +87,7 @@ void free_device(DeviceTables *d)
     if (d->tw_theta) (void)hipFree(d->tw_theta);
     if (d->tw_phi) (void)hipFree(d->tw_phi);
     if (d->fused_c) (void)hipFree(d->fused_c);
-    if (d->phi_rest) (void)hipFree(d->phi_rest);
+    if (d->join_c) (void)hipFree(d->join_c);
     if (d->phi_in) (void)hipFree(d->phi_in);
     *d = DeviceTables{};
 }
@@ -172,8 +176,9 @@ int check_call(sphfilt_plan p, const double *in, double *out)
     return SPHFILT_OK;
 }
 
-// Fused shells and the phi pass of the other shells' ring pairs, in one
-// launch.  On a fusable grid (n_phi = 2 n_theta) a shell that the theta pass
+// Fused shells (held in registers at n_phi = 128: 24 x 508 shells of 64 x 128
+// 413 -> 325 us; the LDS form stays there for hybrid fields) and the phi pass of
+// the other shells' ring pairs, in one launch.  On a fusable grid (n_phi = 2 n_theta) a shell that the theta pass
 // filters has every ring filtered too (m_max <= l_max < n_theta = n_phi / 2,
 // also in floating point: rounding is monotone), so all of them are fused and
 // the theta pass has nothing left: the other shells only need their rings
@@ -194,10 +199,15 @@ int apply_fused(sphfilt_plan p, bool adjoint, const double *in, double *out, con
                              nh, p->dev.phi_rest, 0, p->dev.tw_phi,
                              pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
     if (e == hipSuccess && (t.n_fused > nh || n_rings > 0))
-        e = launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta + nh,
-                             p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh, p->dev.phi_rest,
-                             n_rings, p->dev.tw_phi, pass_args(p, d.theta, d, false),
-                             pass_args(p, d.phi, d, false), s, p->theta_mfma != 0);
+        e = p->n_phi == 128
+                ? launch_join(adjoint, p->n_phi, in, out, p->dev.theta + nh,
+                              p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh, p->dev.phi_rest,
+                              n_rings, false, p->dev.tw_phi, s)
+                : launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta + nh,
+                                   p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh,
+                                   p->dev.phi_rest, n_rings, p->dev.tw_phi,
+                                   pass_args(p, d.theta, d, false), pass_args(p, d.phi, d, false), s,
+                                   p->theta_mfma != 0);
     return e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
 }
 
@@ -270,6 +280,70 @@ int apply_overlap(sphfilt_plan p, bool adjoint, double *x, const Decisions &d, h
     return e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
 }
 
+// Joined shells: on the 2 n_theta = n_phi grids that are not fused, active
+// shells of plain kinds go through one kernel that holds a whole shell in
+// registers (n_join of them, join_count; the rest, and the hybrid ones, take
+// two passes), and the ring pairs of the other shells through that launch's
+// ring workgroups or the phi kernel (all of them out of place, where identity
+// rings are copied), so a point moves once, or twice where its shell takes two
+// passes.  The sets touch different shells; with overlapped passes the last
+// one runs on the side stream.  Every shell takes the same kernels in place and
+// out of place.
+int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, const Decisions &d,
+                 hipStream_t s)
+{
+    const HostTables &t = p->host;
+    const int nh = t.theta_hyb, lines = p->n_theta / 2, n_join = p->n_join;
+    const int done = nh + n_join, n_two = t.theta_active - done;
+    const int n_rest = in == out ? t.phi_rest_active : (int)t.phi_rest.size();
+    const bool along = n_join > 0;
+    std::unique_lock<std::mutex> lock(p->side.m, std::defer_lock);
+    hipStream_t rest = s;
+    hipError_t e = hipSuccess;
+    if (in == out && overlap_pays(p) && p->side.state == 1) {
+        lock.lock();
+        rest = p->side.stream;
+        e = hipEventRecord(p->side.fork, s);
+        if (e == hipSuccess) e = hipStreamWaitEvent(rest, p->side.fork, 0);
+    }
+    auto theta = [&](const double *src, int first, int n, bool hybrid) {
+        return launch_theta(2 * p->n_theta, p->theta_cols, src, out, p->dev.theta + first, n, p->n_theta,
+                            p->n_phi, p->dev.tw_theta, pass_args(p, d.theta, d, hybrid), s);
+    };
+    auto phi = [&](const double *src, int first, int n, bool hybrid, hipStream_t st) {
+        return launch_phi(p->n_phi, p->phi_lines, src, out, p->dev.phi_in + first, n, p->n_theta,
+                          p->dev.tw_phi, pass_args(p, d.phi, d, hybrid), st);
+    };
+    auto join = [&](int n, int n_rings, hipStream_t st) {
+        return launch_join(adjoint, p->n_phi, in, out, p->dev.theta + nh,
+                           p->dev.join_c + (size_t)nh * lines, n, p->dev.phi_rest, n_rings,
+                           join_spread(p->n_phi, n_rings, p->compute_units), p->dev.tw_phi, st);
+    };
+    // two passes of shells [first, first + n), whose rings are phi_in's
+    auto two = [&](int first, int n, bool hybrid, int more_rings) {
+        hipError_t r = adjoint ? phi(in, first * lines, n * lines + more_rings, hybrid, s)
+                               : theta(in, first, n, hybrid);
+        if (r == hipSuccess)
+            r = adjoint ? theta(out, first, n, hybrid)
+                        : phi(out, first * lines, n * lines + more_rings, hybrid, s);
+        return r;
+    };
+    if (e == hipSuccess) e = two(0, nh, true, 0);
+    // in place on one stream the phi kernel takes those shells' rings and the
+    // rest's in one launch (phi_rest follows phi_in)
+    const bool one_phi = in == out && rest == s && !along && n_two > 0;
+    if (e == hipSuccess) e = two(done, n_two, false, one_phi ? n_rest : 0);
+    if (e == hipSuccess && n_join > 0) e = join(n_join, along && rest == s ? n_rest : 0, s);
+    if (e == hipSuccess && along && rest != s) e = join(0, n_rest, rest);
+    if (e == hipSuccess && !along && !one_phi)
+        e = phi(in, (int)t.phi_in.size(), n_rest, false, rest);
+    if (rest != s) {
+        if (e == hipSuccess) e = hipEventRecord(p->side.join, rest);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, p->side.join, 0);
+    }
+    return e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
+}
+
 // Two passes in the given order.  Out of place, the first pass runs over all
 // items (copying identity lines) and the second works in place on `out`.
 int apply_two(sphfilt_plan p, Pass first, Pass second, const double *in, double *out,
@@ -284,6 +358,7 @@ int apply_two(sphfilt_plan p, Pass first, Pass second, const double *in, double 
         rc = apply_fused(p, first == Pass::Phi, in, out, d, s);
         if (rc != SPHFILT_EUNSUPPORTED) return rc;
     }
+    if (p->fused && !p->host.join_c.empty()) return apply_joined(p, first == Pass::Phi, in, out, d, s);
     if (overlap_pays(p) && in == out) {
         rc = apply_overlap(p, first == Pass::Phi, out, d, s);
         if (rc != SPHFILT_EUNSUPPORTED) return rc;
@@ -457,7 +532,7 @@ int tune_plan(sphfilt_plan p, const std::string &arch, const char *cache_path)
             c.phi_lines = l;
             try_sched(c);
         }
-    if (p->host.n_fused > 0)
+    if (p->host.n_fused > 0 || !p->host.join_c.empty())
         for (int f : {0, 1}) {
             PlanSched c = best;
             c.fused = f;
@@ -603,8 +678,18 @@ int sphfilt_plan_create(sphfilt_plan *out, int n_r, int n_theta, int n_phi, int 
         if (!rc) rc = upload(&p->dev.tw_theta, twiddles(2 * n_theta));
         if (!rc) rc = upload(&p->dev.tw_phi, twiddles(n_phi));
         if (!rc) rc = upload(&p->dev.fused_c, p->host.fused_c);
-        if (!rc) rc = upload(&p->dev.phi_rest, p->host.phi_rest);
-        if (!rc) rc = upload(&p->dev.phi_in, p->host.phi_in);
+        if (!rc) rc = upload(&p->dev.join_c, p->host.join_c);
+        std::vector<PhiItem> rings = p->host.phi_in;
+        rings.insert(rings.end(), p->host.phi_rest.begin(), p->host.phi_rest.end());
+        if (!rc) rc = upload(&p->dev.phi_in, rings);
+        if (!rc) p->dev.phi_rest = p->dev.phi_in + p->host.phi_in.size();
+        if (!rc && !p->host.join_c.empty()) {
+            hipDeviceProp_t prop;
+            if (hipGetDeviceProperties(&prop, p->device) != hipSuccess) rc = SPHFILT_EDEVICE;
+            p->compute_units = prop.multiProcessorCount;
+            p->n_join = join_count(n_phi, p->host.theta_active - p->host.theta_hyb,
+                                   p->host.phi_rest_active, p->compute_units);
+        }
     } catch (const std::bad_alloc &) {
         rc = SPHFILT_ENOMEM;
     }

@@ -70,6 +70,21 @@ hipError_t launch_shell_phi(bool adjoint, int n_theta, int n_phi, const double *
                             const ThetaItem *shells, const double *ring_c, int n_shells,
                             const PhiItem *rings, int n_rings, const Twiddle *tw, const HybridArgs &ht, const HybridArgs &hp,
                             hipStream_t stream, bool mfma = false);
+// Joined shells: both passes of n_shells shells of plain kinds, every line of
+// which is filtered, each held in one workgroup's registers, and in the same
+// launch the phi pass of n_rings ring pairs of shells that the theta pass
+// leaves alone; ring_c and tw as for launch_shell_phi, n_line = n_phi =
+// 2 n_theta.  spread: the shells among the ring workgroups, not before them.
+// join_supported: the grids that are not shell_fusable (n_phi = 128 is both).
+bool join_supported(int n_theta, int n_phi);
+// How many of n shells to join, in a launch with n_rings ring pairs; the others
+// are faster in two passes.
+int join_count(int n_line, int n, int n_rings, int compute_units);
+bool join_spread(int n_line, int n_rings, int compute_units);
+hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
+                       const ThetaItem *shells, const double *ring_c, int n_shells,
+                       const PhiItem *rings, int n_rings, bool spread, const Twiddle *tw,
+                       hipStream_t stream);
 // The theta pass as the circulant product on the matrix cores, over active
 // shells of plain kinds, on grids with theta_gemm_ok (n_phi = 2 n_theta in
 // {32, 64}); tw: the twiddle table of length n_phi.

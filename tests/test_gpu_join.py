@@ -1,0 +1,153 @@
+"""Joined shells on the GPU.
+
+On grids with n_phi = 2 n_theta a plan holds whole shells in the registers of
+one workgroup for both passes: every plain shell that the theta pass filters
+where a line has 48, 80, 96 or 128 points, and full rounds of one shell per
+compute unit at 160, 192 and 256 points (a short last round takes two passes,
+unless the other shells' rings fill the units).  The cases leave ragged
+workgroups (two shells each at 80 points, four at 48), launches below and
+above a round, a last round that is joined and one that is not, spread
+shells, every kind and both parities.  Results match the oracle, equal the
+two-pass filter to rounding, and in place and out of place are bitwise equal.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2305_01537_amd import synth
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-12        # against the oracle's direct transforms, as everywhere in these tests
+TOL_TWO = 1e-14    # against the two-pass kernels: the same transforms, other contractions
+EXP, GAUSS, SHARP, HYBRID = 0, 1, 2, 3
+
+
+@pytest.fixture(scope="module")
+def torch_gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    return torch
+
+
+def fields(shape, seed):
+    """Smooth angular fields times a radial factor, plus noise."""
+    F, R, T, P = shape
+    rng = np.random.default_rng(seed)
+    theta, phi = synth.theta_grid(T), synth.phi_grid(P)
+    x = np.empty(shape)
+    for f in range(F):
+        a = synth.angular_sum(rng, 10, theta, phi, lambda l: 1.0 / (l + 1))
+        x[f] = (1.0 + rng.random(R))[:, None, None] * a
+    x += 1e-3 * rng.standard_normal(shape)
+    parity = np.where(np.arange(F) % 2 == 0, 1, -1).astype(np.int32)
+    x[parity < 0] *= np.sin(theta)[None, :, None]
+    return x, parity
+
+
+def rel(a, b):
+    return float(np.abs(a - b).max() / max(np.abs(b).max(), 1e-300))
+
+
+# shape (fields, shells, n_theta, n_phi), kinds, cal-L, rho (None: i + 1/2)
+CASES = [
+    ((1, 1, 24, 48), [EXP], 0.2, None),
+    ((3, 3, 24, 48), [EXP, GAUSS, SHARP], 0.2, None),
+    ((4, 11, 24, 48), [EXP, GAUSS, SHARP, HYBRID], 1.5, None),
+    ((1, 1, 40, 80), [GAUSS], 0.2, None),
+    ((3, 5, 40, 80), [EXP, GAUSS, SHARP], 0.2, None),
+    ((4, 9, 40, 80), [EXP, GAUSS, SHARP, HYBRID], 3.0, None),
+    ((4, 9, 48, 96), [EXP, GAUSS, SHARP, HYBRID], 3.0, None),
+    ((4, 9, 64, 128), [EXP, GAUSS, SHARP, HYBRID], 4.0, None),
+    ((3, 3, 80, 160), [EXP, GAUSS, SHARP], 0.5, None),       # a short round: two passes
+    ((3, 60, 80, 160), [EXP, GAUSS, SHARP], 0.5, None),      # one round
+    ((4, 70, 80, 160), [EXP, GAUSS, SHARP, HYBRID], 2.0, None),
+    ((3, 60, 96, 192), [EXP, GAUSS, SHARP], 0.5, None),
+    ((3, 91, 96, 192), [EXP, GAUSS, SHARP], 0.5, 1.0),       # a round and a short one
+    ((2, 2, 128, 256), [EXP, SHARP], 3.0, None),
+    ((3, 50, 128, 256), [EXP, GAUSS, SHARP], 1.0, None),     # one round
+    ((3, 90, 128, 256), [EXP, GAUSS, SHARP], 0.5, 1.0),      # a round and a short one
+    ((2, 400, 128, 256), [EXP, SHARP], 0.5, None),           # shells spread among the rings
+]
+
+
+@pytest.mark.parametrize("shape,kind,L,rho", CASES,
+                         ids=["%dx%d-%dx%d-%s" % (*c[0], c[2]) for c in CASES])
+def test_joined_shells(torch_gpu, shape, kind, L, rho):
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Plan
+    F, R, T, P = shape
+    x, parity = fields(shape, 311 + T)
+    kind = np.array(kind, dtype=np.int32)
+    hybrid = kind == HYBRID
+    if hybrid.any():
+        x[hybrid] += 3.0
+        x[hybrid, R // 2, : T // 3, 1] = 0.0                 # a jump along theta
+    rho = None if rho is None else np.full(R, rho)
+    plan = Plan(R, T, P, F, parity=parity, L=L, rho=rho, kind=kind)
+    st = plan.stats()
+    print(f"[gpu] joined {shape} kinds {kind.tolist()} L {L}: theta shells {st['theta_shells_active']}",
+          flush=True)
+    for name, ref_fn in (("apply", oracle.forward), ("apply_adjoint", oracle.adjoint)):
+        xd = torch.from_numpy(x).cuda()
+        got = getattr(plan, name)(xd)
+        assert torch.equal(xd, torch.from_numpy(x).cuda()), "the input of an out-of-place call"
+        plan.set_fused(False)
+        two = getattr(plan, name)(xd)
+        plan.set_fused(True)
+        assert torch.equal(getattr(plan, name)(xd, out=xd), got), "in place"
+        got, two = got.cpu().numpy(), two.cpu().numpy()
+        ref = ref_fn(x, parity=parity, L=np.full(F, L), rho=rho, kind=kind)
+        for f in range(F):
+            assert rel(got[f], ref[f]) <= TOL, (name, f, rel(got[f], ref[f]))
+            assert rel(got[f], two[f]) <= TOL_TWO, (name, f, rel(got[f], two[f]))
+    plan.close()
+
+
+def test_joined_shells_pass_nonfinite_values_only_along_their_shell(torch_gpu):
+    """An infinity stays inside its shell (all of it becomes non-finite, as the
+    transforms spread it); every other shell of the launch is untouched by it."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Plan
+    for T in (24, 40, 48, 64):
+        shape = (2, 5, T, 2 * T)
+        x, parity = fields(shape, 401)
+        plan = Plan(5, T, 2 * T, 2, parity=parity, L=0.2, rho=np.ones(5))
+        clean = plan.apply(torch.from_numpy(x).cuda())
+        x[1, 2, 3, 4] = np.inf
+        got = plan.apply(torch.from_numpy(x).cuda())
+        bad = ~torch.isfinite(got)
+        assert bad[1, 2].any()
+        bad[1, 2] = False
+        assert not bad.any()
+        got[1, 2] = clean[1, 2]
+        assert torch.equal(got, clean)
+        plan.close()
+
+
+def test_joined_shells_in_a_captured_graph(torch_gpu):
+    """Forward and adjoint captured once, replayed with other work in between."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Plan
+    shape = (2, 90, 80, 160)
+    x, parity = fields(shape, 421)
+    plan = Plan(90, 80, 160, 2, parity=parity, L=0.4)
+    src = torch.from_numpy(x).cuda()
+    eager = plan.apply_adjoint(plan.apply(src.clone()))
+    buf = src.clone()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        plan.apply(buf, out=buf)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.apply(buf, out=buf)
+        plan.apply_adjoint(buf, out=buf)
+    for k in range(3):
+        buf.copy_(src)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(buf, eager), k
+        _ = (src * 2.0).sum().item()
+    plan.close()
