@@ -322,11 +322,12 @@ int sphfilt_plan_get_overlap(sphfilt_plan plan, int *mode);
 /* ======================================================================
  * Batched filter: many uneven spherical patches in one launch.
  *
- * Each patch is filtered exactly as by its own plan (same operator, same
- * per-line arithmetic: bit-identical results to a two-pass plan without
- * hybrid fields, equal to rounding otherwise); the batch schedules every
- * patch's theta groups and ring-pair groups as items of one persistent
- * kernel, replayed from a captured HIP graph.  This is the GPU counterpart of
+ * Each patch is filtered as by its own plan (the same operator; equal to
+ * rounding, and without fused or joined shells and hybrid fields bit-identical
+ * to a two-pass plan); the batch joins the shells of its plain n_phi =
+ * 2 * n_theta patches in one launch per line length, schedules every other
+ * patch's theta groups and ring-pair groups as items of one work list, and
+ * replays all of it from a captured HIP graph.  This is the GPU counterpart of
  * the paper's OpenMP loop over many line transforms on one rank (Sec. II.B).
  * ====================================================================== */
 
@@ -411,7 +412,8 @@ int sphfilt_batch_apply_noalloc(sphfilt_batch batch, const double *const *ins,
 int sphfilt_batch_tune(sphfilt_batch batch, const char *tune_cache_path);
 
 /*
- * Schedule of the batch kernel.
+ * Schedule of the batch kernel, which runs the patches that are not joined
+ * (see sphfilt_batch_set_fused).
  *   split              0: one persistent kernel; second-pass items wait on
  *                      per-shell counters of the first pass.  1: two
  *                      persistent kernels, first pass then second pass.
@@ -419,7 +421,8 @@ int sphfilt_batch_tune(sphfilt_batch batch, const char *tune_cache_path);
  *                      first-pass item writes (in place: the rings of
  *                      theta-idle shells) run on a parallel branch of the
  *                      graph, on a stream of the batch, alongside the first
- *                      pass.
+ *                      pass.  An untuned batch starts with 1 (one kernel with
+ *                      its waits measured 1.7 times slower on 64 patches).
  *   workgroups_per_cu  -1: one workgroup per work item (each takes one item
  *                      and exits).  k > 0: a persistent grid of k workgroups
  *                      per compute unit looping over items; 0 = the most
@@ -479,17 +482,19 @@ int sphfilt_batch_status(sphfilt_batch batch, int *device_error);
 int sphfilt_batch_stats(sphfilt_batch batch, sphfilt_stats *out);
 
 /*
- * Fused shells in a batch (as sphfilt_plan_set_fused): a patch with
- * n_phi = 2 * n_theta <= 128 runs its theta-filtered shells as fused items
- * (one HBM round trip for both passes) and the rings of its other shells in
- * the first pass, so it has no second-pass work.
+ * Fused and joined shells in a batch (as sphfilt_plan_set_fused): a patch with
+ * n_phi = 2 * n_theta and no hybrid field has its theta-filtered shells joined
+ * (at 160, 192 and 256 points where the batch has enough of them for a round of
+ * one per compute unit); one with hybrid fields and n_phi <= 128 runs them as
+ * fused items.  Either way both passes take one HBM round trip, the rings of
+ * its other shells go along, and it has no second-pass work.
  *   enable  1 or 0 (every patch in two passes).  The autotuner times both
  *           (when some patch allows fused items) with every schedule and keeps
  *           the fastest; untuned batches start with 1.
  * Changing it drops the batch's captured graphs and work lists (they are
  * rebuilt on the next call) after synchronising the device.  get_fused
- * reports the setting and the number of shells fused (NULL outputs are
- * skipped).
+ * reports the setting and the number of shells of n_phi <= 128 it covers (NULL
+ * outputs are skipped).
  */
 int sphfilt_batch_set_fused(sphfilt_batch batch, int enable);
 int sphfilt_batch_get_fused(sphfilt_batch batch, int *enable, int *shells_fused);

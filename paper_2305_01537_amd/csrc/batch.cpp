@@ -1,12 +1,14 @@
 // batch.cpp -- host side of the batched filter: many uneven spherical patches
-// in one persistent kernel launch, replayed from a captured HIP graph, with a
-// schedule picked by an autotuner and remembered in a JSON cache.
+// replayed from a captured HIP graph, with a schedule picked by an autotuner
+// and remembered in a JSON cache.
 //
 // The operation per patch is exactly the plan's (arXiv:2305.01537,
 // Sec. II.A): theta-pass then phi-pass (forward), or the reverse (adjoint).
-// What the batch adds is scheduling: every patch's theta groups and ring-pair
-// groups become items of one work list (see batch_kernels.h), so small patches do
-// not leave the GPU idle and one graph launch covers all of them.
+// What the batch adds is scheduling, so that small patches do not leave the GPU
+// idle and one graph launch covers all of them: the shells of plain patches on
+// n_phi = 2 n_theta grids are joined, in one launch per line length over all
+// patches (kernels_join.hip); every other patch's theta groups and ring-pair
+// groups become items of one work list (see batch_kernels.h).
 #include "../../include/sphfilt.h"
 #include "batch_internal.h"
 #include "host_tables.h"
@@ -38,14 +40,22 @@ struct PatchHost {
     HostTables tables;
     int theta_off = 0, phi_off = 0;   // into the concatenated item arrays
     int phi_rest_off = 0;             // the phi items of theta-idle shells
-    int fc_off = 0;                   // fused shells' ring cutoffs
+    int fc_off = 0;                   // fused or joined shells' ring cutoffs
+    bool plain = true;                // no hybrid field
     int shell_base = 0;               // first global shell id
     int cols = 0;                     // theta sub-tile width (meridian pairs)
     long long n_points = 0;
 };
 
+// The joined items of one line length, [first, first + n) of ModeWork::d_join.
+struct JoinClass {
+    int n_line, first, n;
+};
+
 struct ModeWork {
     bool built = false;
+    BatchWork *d_join = nullptr;
+    std::vector<JoinClass> join;
     int n_work = 0, n_first = 0;
     int n_indep = 0;        // second-pass items at [n_first, n_first + n_indep) touch no
                             // shell a first-pass item writes
@@ -98,7 +108,8 @@ struct sphfilt_batch_s {
     int *d_error = nullptr;
     ModeWork modes[4];
     std::vector<GraphEntry> graphs;
-    int split = 0, wpc = -1;           // schedule: see effective_wpc
+    // two one-workgroup-per-item kernels, the fastest measured form; see effective_wpc
+    int split = 1, wpc = -1;
     int theta_tiles = 1;               // meridian tiles per theta item
     int phi_groups = 1;                // workgroup rounds of ring pairs per phi item
     std::map<int, int> theta_cols;     // theta line length -> sub-tile width (tuned; else default)
@@ -185,14 +196,66 @@ void add_pass(const sphfilt_batch b, int pi, bool theta, bool all, bool second,
 // kernel's second instance.
 bool mixed_radix_line(int n) { return (n & (n - 1)) != 0; }
 
-// A patch whose theta-filtered shells are all fused (n_phi = 2 n_theta in {32, 64, 128},
-// see build_items) runs entirely in the first pass: groups of whole shells
+// A patch with hybrid fields whose theta-filtered shells are all fused (n_phi =
+// 2 n_theta in {32, 64, 128}, see build_items) runs entirely in the first pass: groups of whole shells
 // (both passes, add_fused_shells), and the ring pairs of its theta-idle shells
 // (add_rest_rings; out of place also their identity rings, copied).  Nothing
 // waits for these items.
 bool patch_fused(const sphfilt_batch b, const PatchHost &p)
 {
-    return b->fused && p.tables.n_fused > 0 && p.tables.n_fused == p.tables.theta_active;
+    return b->fused && !p.plain && p.tables.n_fused > 0 && p.tables.n_fused == p.tables.theta_active;
+}
+
+// A patch whose theta-filtered shells can all be joined (held whole by one
+// workgroup, kernels_join.hip): n_phi = 2 n_theta, no hybrid field, and every
+// ring of those shells filtered.
+bool patch_joinable(const sphfilt_batch b, const PatchHost &p)
+{
+    const HostTables &t = p.tables;
+    return b->fused && p.plain && p.n_phi == 2 * p.n_theta &&
+           (t.theta_active == t.n_fused || !t.join_c.empty());
+}
+
+// The joined items of line length N: shells, and the ring pairs of the
+// theta-idle shells, of every joinable patch; shells first, or spread over the
+// first 4/5 of the rings (join_spread).  64 patches of 16 x 32 to 128 x 256 at
+// cal-L = 3: 1952 us as items of the one-kernel schedule with its waits, about
+// 1130 as two launches of fused and two-pass items, 890 joined (4.1 TB/s of
+// 16 B per touched point); 24 patches with radix-3 lines 838 -> 371.  None if the class has too few shells
+// for a round of one per compute unit (join_count): two passes are faster.
+std::vector<BatchWork> join_items(const sphfilt_batch b, int N, bool all)
+{
+    std::vector<BatchWork> shells, rings;
+    const int S = join_group_shells(N), L = join_group_rings(N);
+    int n_shells = 0, n_rings = 0;
+    for (int pi = 0; pi < (int)b->patches.size(); ++pi) {
+        const PatchHost &p = b->patches[(size_t)pi];
+        if (p.n_phi != N || !patch_joinable(b, p)) continue;
+        const int ns = p.tables.theta_active;
+        const int nr = all ? (int)p.tables.phi_rest.size() : p.tables.phi_rest_active;
+        n_shells += ns;
+        n_rings += p.tables.phi_rest_active;
+        for (int g = 0; g < ns; g += S)
+            shells.push_back(BatchWork{pi, 2, 0, p.theta_off + g, (int16_t)std::min(S, ns - g), 0, 0, 0,
+                                       p.fc_off + g * (N / 4), 1});
+        for (int c = 0; c < nr; c += L)
+            rings.push_back(BatchWork{pi, 1, 0, p.phi_rest_off + c, (int16_t)std::min(L, nr - c), 0, 0, 0,
+                                      0, 1});
+    }
+    if (join_count(N, n_shells, n_rings, b->n_cu) == 0) return {};
+    if (!join_spread(N, n_rings, b->n_cu)) {
+        shells.insert(shells.end(), rings.begin(), rings.end());
+        return shells;
+    }
+    std::vector<BatchWork> out;
+    const size_t among = rings.size() * 4 / 5;
+    size_t r = 0;
+    for (size_t i = 0; i < shells.size(); ++i) {
+        out.push_back(shells[i]);
+        for (; r < among * (i + 1) / shells.size(); ++r) out.push_back(rings[r]);
+    }
+    out.insert(out.end(), rings.begin() + (long)r, rings.end());
+    return out;
 }
 
 void add_fused_shells(const sphfilt_batch b, int pi, bool adjoint, std::vector<BatchWork> *work)
@@ -221,13 +284,29 @@ int build_mode(sphfilt_batch b, int mode)
     ModeWork &m = b->modes[mode];
     if (m.built) return SPHFILT_OK;
     const bool adjoint = mode & 1, inplace = mode & 2;
-    std::vector<BatchWork> work;
+    std::vector<BatchWork> work, join;
     std::vector<int> shells;
+    // the longest lines first: their workgroups run longest
+    m.join.clear();
+    for (int N : {256, 192, 160, 128, 96, 80, 64, 48, 32}) {
+        const std::vector<BatchWork> items = join_items(b, N, !inplace);
+        if (items.empty()) continue;
+        m.join.push_back(JoinClass{N, (int)join.size(), (int)items.size()});
+        join.insert(join.end(), items.begin(), items.end());
+    }
+    auto joined = [&](const PatchHost &p) {
+        if (!patch_joinable(b, p)) return false;
+        for (const JoinClass &c : m.join)
+            if (c.n_line == p.n_phi) return true;
+        return false;
+    };
     // fused shell groups first: they hold a workgroup longest (a whole shell,
     // both passes), so they start before the short items rather than trail them
     for (int p = 0; p < (int)b->patches.size(); ++p)
-        if (patch_fused(b, b->patches[(size_t)p])) add_fused_shells(b, p, adjoint, &work);
+        if (!joined(b->patches[(size_t)p]) && patch_fused(b, b->patches[(size_t)p]))
+            add_fused_shells(b, p, adjoint, &work);
     for (int p = 0; p < (int)b->patches.size(); ++p) {
+        if (joined(b->patches[(size_t)p])) continue;
         if (patch_fused(b, b->patches[(size_t)p]))
             add_rest_rings(b, p, !inplace, &work);
         else
@@ -236,7 +315,7 @@ int build_mode(sphfilt_batch b, int mode)
     const int n_first = (int)work.size();
     std::vector<BatchWork> second;
     for (int p = 0; p < (int)b->patches.size(); ++p)
-        if (!patch_fused(b, b->patches[(size_t)p]))
+        if (!joined(b->patches[(size_t)p]) && !patch_fused(b, b->patches[(size_t)p]))
             add_pass(b, p, adjoint, false, true, &second, &shells);
     std::vector<int> need((size_t)std::max(1, b->n_shells_total), 0);
     for (int k = 0; k < n_first; ++k)
@@ -254,6 +333,7 @@ int build_mode(sphfilt_batch b, int mode)
     while (n_indep < (int)second.size() && independent(second[(size_t)n_indep])) ++n_indep;
     work.insert(work.end(), second.begin(), second.end());
     int rc = upload(&m.d_work, work);
+    if (!rc) rc = upload(&m.d_join, join);
     if (!rc) rc = upload(&m.d_shells, shells);
     if (!rc) rc = upload(&m.d_need, need);
     if (rc) return rc;
@@ -287,9 +367,10 @@ constexpr int kFaultSpinLimit = 64;
 
 // Enqueue the reset kernel and the persistent kernel(s) of `m` on stream s
 // (a capture stream, or the caller's stream for the allocation-free call).
-int record(sphfilt_batch b, const ModeWork &m, int split, int wpc_setting, const CallScratch &sc,
+int record(sphfilt_batch b, int mode, int split, int wpc_setting, const CallScratch &sc,
            int wait_fault, hipStream_t s)
 {
+    const ModeWork &m = b->modes[mode];
     const int wpc = effective_wpc(b, wpc_setting);
     const int grid = wpc < 0 ? 0 : wpc * b->n_cu;
     const int spin = wait_fault ? kFaultSpinLimit : kSpinLimit, bias = wait_fault ? 1 : 0;
@@ -298,6 +379,10 @@ int record(sphfilt_batch b, const ModeWork &m, int split, int wpc_setting, const
                             b->d_ph, b->d_fc, m.d_shells, sc.counters, m.d_need, ticket, sc.error, deps, spin, bias, b->variant, st);
     };
     hipError_t e = launch_batch_reset(sc.counters, b->n_shells_total, sc.tickets, 3, sc.error, s);
+    for (const JoinClass &c : m.join)
+        if (e == hipSuccess)
+            e = launch_batch_join(c.n_line, mode & 1, m.d_join + c.first, c.n, sc.ins, sc.outs, b->d_th,
+                                  b->d_ph, b->d_fc, b->d_tw[c.n_line], s);
     if (e != hipSuccess) return SPHFILT_EDEVICE;
     if (split == 2 && m.n_indep > 0) {
         // fork: the independent second-pass items on the side stream, the
@@ -356,7 +441,7 @@ int get_graph(sphfilt_batch b, int mode, const double *const *ins, double *const
         if (e != hipSuccess) rc = SPHFILT_EDEVICE;
         if (!rc) {
             const CallScratch sc{b->d_counters, b->d_tickets, b->d_error, g.d_ins, g.d_outs};
-            const int rr = record(b, b->modes[mode], g.split, g.wpc, sc, g.wait_fault,
+            const int rr = record(b, mode, g.split, g.wpc, sc, g.wait_fault,
                                   b->capture_stream);
             e = hipStreamEndCapture(b->capture_stream, &g.graph);
             rc = rr ? rr : (e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE);
@@ -381,6 +466,7 @@ void free_work(sphfilt_batch b)
     b->graphs.clear();
     for (ModeWork &m : b->modes) {
         if (m.d_work) (void)hipFree(m.d_work);
+        if (m.d_join) (void)hipFree(m.d_join);
         if (m.d_shells) (void)hipFree(m.d_shells);
         if (m.d_need) (void)hipFree(m.d_need);
         m = ModeWork{};
@@ -481,7 +567,7 @@ int launch_noalloc(sphfilt_batch b, const double *const *ins, double *const *out
     if (noalloc_set_pointers(base, ins, outs, (int)b->patches.size(), stream) != hipSuccess)
         return SPHFILT_EDEVICE;
     b->last_noalloc = 1;
-    return record(b, m, b->split, b->wpc, sc, fault("wait") ? 1 : 0, stream);
+    return record(b, mode, b->split, b->wpc, sc, fault("wait") ? 1 : 0, stream);
 }
 
 // Time the current schedule on scratch fields: the median over `reps` rounds
@@ -524,7 +610,7 @@ int time_schedule(sphfilt_batch b, const std::vector<double *> &bufs, hipStream_
 constexpr int kLines[9] = {32, 48, 64, 80, 96, 128, 160, 192, 256};
 
 struct Sched {
-    int fused = 1, split = 0, wpc = -1, theta_tiles = 1, phi_groups = 1;
+    int fused = 1, split = 1, wpc = -1, theta_tiles = 1, phi_groups = 1;
     std::map<int, int> cols;      // theta line length -> sub-tile width (absent: default)
 };
 
@@ -685,7 +771,7 @@ int tune(sphfilt_batch b, const char *cache_path)
     if (!rc) rc = warm_batch(b, bufs, s);
     try_sched(start);
     bool any_fused = false;
-    for (const PatchHost &p : b->patches) any_fused |= p.tables.n_fused > 0 && p.tables.n_fused == p.tables.theta_active;
+    for (const PatchHost &p : b->patches) any_fused |= p.n_phi == 2 * p.n_theta && p.tables.theta_active > 0;
     auto split_wpc = [&](int fused) {
         for (int split = 0; split <= 2 && !rc; ++split)
             for (int wpc = -1; wpc <= b->max_wpc && !rc; ++wpc) {
@@ -703,8 +789,8 @@ int tune(sphfilt_batch b, const char *cache_path)
     for (int n : kLines) {
         bool has = false;
         for (const PatchHost &p : b->patches)
-            has |= 2 * p.n_theta == n && !(best.fused && p.tables.n_fused > 0 &&
-                                           p.tables.n_fused == p.tables.theta_active);
+            has |= 2 * p.n_theta == n &&
+                   !(best.fused && (patch_joinable(b, p) || patch_fused(b, p)));
         if (!has) continue;
         const Sched base = best;
         for (int w : {4, 8, 16, 32, 64}) {
@@ -826,6 +912,8 @@ int sphfilt_batch_create(sphfilt_batch *out, int n_patches, const sphfilt_patch_
             all_ph.insert(all_ph.end(), h.tables.phi_rest.begin(), h.tables.phi_rest.end());
             h.fc_off = (int)all_fc.size();
             all_fc.insert(all_fc.end(), h.tables.fused_c.begin(), h.tables.fused_c.end());
+            all_fc.insert(all_fc.end(), h.tables.join_c.begin(), h.tables.join_c.end());
+            h.plain = !hybrid_args(&d.cut, d.n_fields).present;
             b->patches.push_back(std::move(h));
         }
         th = (long long)all_th.size();
@@ -1067,7 +1155,7 @@ int sphfilt_batch_get_fused(sphfilt_batch batch, int *enable, int *shells_fused)
     if (!batch) return SPHFILT_EINVAL;
     int n = 0;
     for (const PatchHost &p : batch->patches)
-        if (patch_fused(batch, p)) n += p.tables.n_fused;
+        if (batch->fused) n += p.tables.n_fused;
     if (enable) *enable = batch->fused;
     if (shells_fused) *shells_fused = n;
     return SPHFILT_OK;

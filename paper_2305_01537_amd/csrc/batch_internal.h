@@ -100,6 +100,18 @@ hipError_t launch_batch(int grid, const BatchWork *work, int n_work, const Batch
 // `variant` per compute unit.
 int batch_blocks_per_cu(int variant);
 
+// Joined items (kernels_join.hip): the shells and rings of the patches whose
+// shells are all held whole (n_phi = 2 n_theta, plain kinds), one list and one
+// launch per line length; item blockIdx.x of `work` is a group of shells (pass
+// 2, aux their ring cutoffs) or of ring pairs of theta-idle shells (pass 1).
+// They wait for nothing and nothing waits for them.
+hipError_t launch_batch_join(int n_line, bool adjoint, const BatchWork *work, int n_work,
+                             const double *const *ins, double *const *outs, const ThetaItem *th,
+                             const PhiItem *ph, const double *fc, const Twiddle *tw, hipStream_t s);
+// Shells and ring pairs per workgroup of that launch.
+int join_group_shells(int n_line);
+int join_group_rings(int n_line);
+
 // ---- the allocation-free entry point's device scratch (batch.hip) --------
 // One statically allocated array per device holds the batch kernel's
 // counters, tickets, error word and the per-call pointer tables:

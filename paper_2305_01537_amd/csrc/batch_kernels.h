@@ -16,21 +16,20 @@
 // additionally turns a logic error into a flagged error instead of a hang.
 //
 // The per-line work is done by the same workers as the per-plan kernels
-// (line_filter.h).  Patches whose shells fit in LDS (n_phi = 2 n_theta <=
-// 128) run their theta-filtered shells as fused items (both passes, one HBM
-// round trip, as a plan does) and the rings of their other shells in the
-// first pass: such a patch has no second-pass work.
+// (line_filter.h).  Plain patches on n_phi = 2 n_theta grids are not here: their
+// shells are joined (kernels_join.hip).  A patch with hybrid fields and
+// n_phi = 2 n_theta <= 128 runs its theta-filtered shells as fused items (both
+// passes, one HBM round trip, as a plan does) and the rings of its other shells
+// in the first pass: such a patch has no second-pass work.
 #pragma once
 #include "batch_internal.h"
 #include "line_filter.h"
 
 namespace sphfilt {
 
-// LDS of the largest worker: the staged shells of the fused worker
-// (ShellShape<128>::lds), which also covers the line scratch of every
-// theta/phi group, hybrid spectra included; for the instance that also
-// takes the lengths that are not powers of two (MIXED) it is the larger of
-// that and their line scratch (which fits in it with the current splits).
+// LDS of the largest worker: the line scratch of every theta/phi group and, in
+// the hybrid-capable instances, the staged shells of the fused worker
+// (ShellShape<128>::lds; plain patches' shells are joined, kernels_join.hip).
 template <int N, bool HYB>
 constexpr int batch_line_lds()
 {
@@ -39,7 +38,9 @@ constexpr int batch_line_lds()
 template <bool HYB, bool MIXED>
 constexpr int batch_lds()
 {
-    constexpr int a = ShellShape<128>::lds;
+    constexpr int c = batch_line_lds<128, HYB>() > batch_line_lds<256, HYB>() ? batch_line_lds<128, HYB>()
+                                                                           : batch_line_lds<256, HYB>();
+    constexpr int a = HYB && ShellShape<128>::lds > c ? ShellShape<128>::lds : c;
     constexpr int b = batch_line_lds<96, HYB>() > batch_line_lds<192, HYB>() ? batch_line_lds<96, HYB>()
                                                                           : batch_line_lds<192, HYB>();
     return MIXED && b > a ? b : a;
@@ -60,9 +61,9 @@ static_assert(batch_lds_fits<32, false>() && batch_lds_fits<64, false>() &&
 // registers).  One-shot: two.  Persistent: two for the plain forms, one for
 // the hybrid forms (about 270 registers: at two waves they would spill).
 template <bool HYB, bool MIXED>
-constexpr int oneshot_waves() { return 2; }
+constexpr int oneshot_waves() { return HYB ? 2 : 3; }
 template <bool HYB, bool MIXED>
-constexpr int persistent_waves() { return HYB ? 1 : 2; }
+constexpr int persistent_waves() { return HYB ? 1 : 3; }
 
 // Hybrid lines in a batch decide from their data; decisions are not recorded.
 __device__ __forceinline__ HybridArgs batch_hybrid(const BatchPatchDev &pd)
@@ -179,11 +180,13 @@ __device__ __forceinline__ void run_item(const BatchArgs &a, int k, int lane, do
             }
             break;
         }
-    } else if (w.pass == 2) {
-        switch (pd.n_phi) {
-        case 32: fused_item<32, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
-        case 64: fused_item<64, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
-        default: fused_item<128, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
+    } else if (HYB && w.pass == 2) {
+        if constexpr (HYB) {
+            switch (pd.n_phi) {
+            case 32: fused_item<32, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
+            case 64: fused_item<64, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
+            default: fused_item<128, HYB>(w, pd, src, dst, a.th, a.fc, lds, flags, lane); break;
+            }
         }
     } else {
         switch (pd.n_phi) {

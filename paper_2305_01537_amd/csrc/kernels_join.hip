@@ -1,6 +1,7 @@
-// kernels_join.hip -- per-plan kernels that run both passes of whole shells in
-// registers (shell_join.h), double FFT filter (arXiv:2305.01537, Sec. II.A)
-// for gfx950, FP64.
+// kernels_join.hip -- kernels that run both passes of whole shells in registers
+// (shell_join.h), per plan and per batch, double FFT filter
+// (arXiv:2305.01537, Sec. II.A) for gfx950, FP64.
+#include "batch_internal.h"
 #include "shell_join.h"
 
 namespace sphfilt {
@@ -11,6 +12,29 @@ template <int N>
 constexpr int join_waves()
 {
     return N == 256 || N == 128 ? 4 : 3;
+}
+
+// One workgroup's shells; stages the twiddle table.
+template <int N, bool ADJ>
+__device__ __forceinline__ void join_group(const double *in, double *out, const ThetaItem *__restrict__ shells,
+                                           const double *__restrict__ ring_c, int n_valid,
+                                           const Twiddle *__restrict__ tw, Twiddle *table, double *lds)
+{
+    using S = JoinShape<N>;
+    for (int i = threadIdx.x; i < S::table; i += S::width) table[i] = tw[i];
+    auto run = [&](auto kind) {
+        join_block<N, ADJ, decltype(kind)::value>(in, out, shells, ring_c, n_valid, table, lds);
+    };
+    if constexpr (S::shells > 1) {
+        run(std::integral_constant<int, -1>{});
+    } else {
+        // one shell per workgroup: one kind, and no registers held across the
+        // branches between the kinds' masks
+        const int kind = shells[0].flags & kKindMask;
+        if (kind == 0) run(std::integral_constant<int, 0>{});
+        else if (kind == 1) run(std::integral_constant<int, 1>{});
+        else run(std::integral_constant<int, 2>{});
+    }
 }
 
 // Shells and, in the same grid, ring pairs of other shells (as many as a
@@ -45,23 +69,29 @@ void join_kernel(const double *in, double *out, const ThetaItem *__restrict__ sh
                                          nullptr, HybridArgs{}, threadIdx.x);
         return;
     }
-    for (int i = threadIdx.x; i < S::table; i += S::width) table[i] = tw[i];
     const int first = group * S::shells;
-    const int n_valid = min(S::shells, n_shells - first);
-    auto run = [&](auto kind) {
-        join_block<N, ADJ, decltype(kind)::value>(in, out, shells + first,
-                                                  ring_c + (size_t)first * S::lines, n_valid, table, lds);
-    };
-    if constexpr (S::shells > 1) {
-        run(std::integral_constant<int, -1>{});
-    } else {
-        // one shell per workgroup: one kind, and no registers held across the
-        // branches between the kinds' masks
-        const int kind = shells[first].flags & kKindMask;
-        if (kind == 0) run(std::integral_constant<int, 0>{});
-        else if (kind == 1) run(std::integral_constant<int, 1>{});
-        else run(std::integral_constant<int, 2>{});
-    }
+    join_group<N, ADJ>(in, out, shells + first, ring_c + (size_t)first * S::lines,
+                       min(S::shells, n_shells - first), tw, table, lds);
+}
+
+// The same for a batch: one item per workgroup, in list order.
+template <int N, bool ADJ>
+__global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N>())))
+void batch_join_kernel(const BatchWork *__restrict__ work, const double *const *ins, double *const *outs,
+                       const ThetaItem *__restrict__ th, const PhiItem *__restrict__ ph,
+                       const double *__restrict__ fc, const Twiddle *__restrict__ tw)
+{
+    using S = JoinShape<N>;
+    __shared__ double lds[S::lds];
+    __shared__ Twiddle table[S::table];
+    const BatchWork w = work[blockIdx.x];
+    const double *in = ins[w.patch];
+    double *out = outs[w.patch];
+    if (w.pass == 1)
+        phi_block<N, S::width / S::N2, false, true>(in, out, ph + w.first, w.n_valid, N / 2, tw, lds,
+                                                    nullptr, HybridArgs{}, threadIdx.x);
+    else
+        join_group<N, ADJ>(in, out, th + w.first, fc + w.aux, w.n_valid, tw, table, lds);
 }
 
 template <int N>
@@ -138,6 +168,54 @@ hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
     case 256: return join_go<256>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+namespace {
+// f(std::integral_constant<int, N>) for the line length n_line
+template <typename F>
+auto with_line(int n_line, F &&f)
+{
+    switch (n_line) {
+    case 32: return f(std::integral_constant<int, 32>{});
+    case 48: return f(std::integral_constant<int, 48>{});
+    case 64: return f(std::integral_constant<int, 64>{});
+    case 80: return f(std::integral_constant<int, 80>{});
+    case 96: return f(std::integral_constant<int, 96>{});
+    case 128: return f(std::integral_constant<int, 128>{});
+    case 160: return f(std::integral_constant<int, 160>{});
+    case 192: return f(std::integral_constant<int, 192>{});
+    default: return f(std::integral_constant<int, 256>{});
+    }
+}
+}  // namespace
+
+int join_group_shells(int n_line)
+{
+    return with_line(n_line, [](auto n) { return JoinShape<decltype(n)::value>::shells; });
+}
+
+int join_group_rings(int n_line)
+{
+    return with_line(n_line, [](auto n) {
+        using S = JoinShape<decltype(n)::value>;
+        return S::width / S::N2;
+    });
+}
+
+hipError_t launch_batch_join(int n_line, bool adjoint, const BatchWork *work, int n_work,
+                             const double *const *ins, double *const *outs, const ThetaItem *th,
+                             const PhiItem *ph, const double *fc, const Twiddle *tw, hipStream_t s)
+{
+    if (n_work <= 0) return hipSuccess;
+    return with_line(n_line, [&](auto n) {
+        constexpr int N = decltype(n)::value;
+        const dim3 grid((unsigned)n_work), block(JoinShape<N>::width);
+        if (adjoint)
+            batch_join_kernel<N, true><<<grid, block, 0, s>>>(work, ins, outs, th, ph, fc, tw);
+        else
+            batch_join_kernel<N, false><<<grid, block, 0, s>>>(work, ins, outs, th, ph, fc, tw);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace sphfilt

@@ -151,3 +151,44 @@ def test_joined_shells_in_a_captured_graph(torch_gpu):
         assert torch.equal(buf, eager), k
         _ = (src * 2.0).sum().item()
     plan.close()
+
+
+@pytest.mark.parametrize("adjoint,inplace", [(False, True), (True, False)])
+def test_joined_shells_in_a_batch(torch_gpu, adjoint, inplace):
+    """A batch joins the shells of its plain n_phi = 2 n_theta patches, per line
+    length over all patches: lengths with a round of shells (160: over two
+    patches, 256: spread among the rings), with too few for one (192: two
+    passes) and shorter ones, beside a patch with a hybrid field and one with
+    another grid.  Every patch matches the oracle, and the call that allocates
+    nothing gives the same bits."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Batch
+    specs = [((2, 40, 80, 160), [EXP, GAUSS], 0.5), ((3, 41, 80, 160), [EXP, SHARP, EXP], 0.5),
+             ((2, 400, 128, 256), [EXP, SHARP], 0.5), ((1, 7, 96, 192), [EXP], 0.5),
+             ((3, 3, 40, 80), [EXP, GAUSS, SHARP], 1.5), ((1, 5, 24, 48), [SHARP], 1.5),
+             ((2, 9, 64, 128), [EXP, HYBRID], 3.0), ((2, 9, 48, 96), [EXP, GAUSS], 3.0),
+             ((2, 5, 32, 64), [EXP, EXP], 1.5), ((1, 9, 16, 32), [GAUSS], 0.5),
+             ((2, 6, 32, 96), [EXP, GAUSS], 1.5), ((1, 3, 16, 32), [EXP], 50.0)]
+    patches, data = [], []
+    for i, (shape, kind, L) in enumerate(specs):
+        x, parity = fields(shape, 500 + i)
+        if HYBRID in kind:
+            x += 3.0
+        F, R, T, P = shape
+        patches.append(dict(n_fields=F, n_r=R, n_theta=T, n_phi=P, parity=parity, L=L,
+                            kind=np.array(kind, dtype=np.int32)))
+        data.append(x)
+    batch = Batch(patches)
+    print(f"[gpu] batch of joined shells adjoint={adjoint} inplace={inplace}", flush=True)
+    xs = [torch.from_numpy(x).cuda() for x in data]
+    got = batch.apply(xs, outs=xs if inplace else None, adjoint=adjoint)
+    again = [torch.from_numpy(x).cuda() for x in data]
+    out2 = batch.apply_noalloc(again, outs=again if inplace else None, adjoint=adjoint)
+    torch.cuda.synchronize()
+    assert batch.status() == 0
+    ref_fn = oracle.adjoint if adjoint else oracle.forward
+    for p, x, g, g2 in zip(patches, data, got, out2):
+        assert torch.equal(g, g2), p
+        ref = ref_fn(x, parity=p["parity"], L=np.full(p["n_fields"], p["L"]), kind=p["kind"])
+        assert rel(g.cpu().numpy(), ref) <= TOL, p
+    batch.close()
