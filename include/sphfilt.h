@@ -235,10 +235,10 @@ int sphfilt_plan_get_schedule(sphfilt_plan plan, int *theta_cols, int *phi_lines
  * differently by the compiler).
  *   enable  1 (the default): fuse where possible; 0: always two passes.
  * The same setting covers joined shells: on grids with n_phi = 2 * n_theta in
- * {48, 80, 96, 160, 192, 256} a shell of a plain kind that the theta pass
- * filters is held in the registers of one workgroup for both passes (at 160,
- * 192 and 256 only as many as fill rounds of one shell per compute unit, see
- * kernels_join.hip; hybrid shells take two passes).  Joined shells are not
+ * {48, 80, 96, 160, 192, 256} a shell that the theta pass filters is held in
+ * the registers of one workgroup for both passes (at 160, 192 and 256 only as
+ * many as fill rounds of one shell per compute unit, see kernels_join.hip;
+ * hybrid shells of 256-point lines take two passes).  Joined shells are not
  * counted in shells_fused and bytes_fused_inplace.
  * set_fused returns SPHFILT_EINVAL for other values; it is not thread-safe
  * against concurrent apply calls on the same plan.  get_fused reports the

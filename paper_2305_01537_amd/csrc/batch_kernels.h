@@ -33,7 +33,7 @@ namespace sphfilt {
 template <int N, bool HYB>
 constexpr int batch_line_lds()
 {
-    return lines_per_256<N>() * line_stride<Split<N>::N1, Split<N>::N2, HYB>();
+    return lines_per_256<N>() * line_lds<Split<N>::N1, Split<N>::N2>();
 }
 template <bool HYB, bool MIXED>
 constexpr int batch_lds()
@@ -57,13 +57,12 @@ static_assert(batch_lds_fits<32, false>() && batch_lds_fits<64, false>() &&
                   batch_lds_fits<96, true>() && batch_lds_fits<160, true>() &&
                   batch_lds_fits<192, true>(),
               "batch LDS holds every worker's line scratch");
-// Waves per SIMD the instances ask for (each then gets at most 256
-// registers).  One-shot: two.  Persistent: two for the plain forms, one for
-// the hybrid forms (about 270 registers: at two waves they would spill).
+// Waves per SIMD the instances ask for: three for the plain ones (up to 160
+// registers), two for the hybrid-capable ones (202 to 209).
 template <bool HYB, bool MIXED>
 constexpr int oneshot_waves() { return HYB ? 2 : 3; }
 template <bool HYB, bool MIXED>
-constexpr int persistent_waves() { return HYB ? 1 : 3; }
+constexpr int persistent_waves() { return HYB ? 2 : 3; }
 
 // Hybrid lines in a batch decide from their data; decisions are not recorded.
 __device__ __forceinline__ HybridArgs batch_hybrid(const BatchPatchDev &pd)

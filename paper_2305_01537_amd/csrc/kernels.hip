@@ -24,7 +24,7 @@ __global__ __launch_bounds__(W) void shell_phi_kernel(
 {
     using S = ShellShape<N, W>;
     constexpr int LINES = W / Split<N>::N2;
-    static_assert(S::lds >= LINES * line_stride<Split<N>::N1, Split<N>::N2, HYB>(), "ring-pair scratch");
+    static_assert(S::lds >= LINES * line_lds<Split<N>::N1, Split<N>::N2>(), "ring-pair scratch");
     __shared__ double lds[S::lds];
     __shared__ int flags[LINES];
     __shared__ double gaux[MFMA ? shell_gemm_aux<N>() : 1];
@@ -190,13 +190,6 @@ static hipError_t shell_phi_go(bool adjoint, const double *in, double *out,
                                hipStream_t s)
 {
     const bool hyb = ht.present != 0;
-    if constexpr (N == 128) {           // plain shells of this size are joined (kernels_join.hip)
-        if (!hyb) return hipErrorInvalidValue;
-        return adjoint ? shell_phi_launch<N, true, true, false>(in, out, shells, ring_c, n_shells, rings,
-                                                                n_rings, tw, ht, hp, s)
-                       : shell_phi_launch<N, false, true, false>(in, out, shells, ring_c, n_shells, rings,
-                                                                 n_rings, tw, ht, hp, s);
-    }
 #define SPHFILT_SHELL_PHI(A, H)                                                                    \
     return shell_phi_launch<N, A, H, MFMA && !H>(in, out, shells, ring_c, n_shells, rings, n_rings, \
                                                  tw, ht, hp, s)
@@ -228,7 +221,6 @@ hipError_t launch_shell_phi(bool adjoint, int n_theta, int n_phi, const double *
     case 64:
         return mfma ? shell_phi_go<64, true>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s)
                     : shell_phi_go<64, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s);
-    case 128: return shell_phi_go<128, false>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, tw, ht, hp, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -8,24 +8,28 @@ namespace sphfilt {
 
 // Waves per SIMD asked for, as many as the workgroups that fit a compute
 // unit's LDS hold: the register cap is 512 / waves.
-template <int N>
+template <int N, bool HYB = false>
 constexpr int join_waves()
 {
-    return N == 256 || N == 128 ? 4 : 3;
+    return N == 256 || (N == 128 && !HYB) ? 4 : 3;
 }
 
 // One workgroup's shells; stages the twiddle table.
-template <int N, bool ADJ>
+template <int N, bool ADJ, bool HYB = false>
 __device__ __forceinline__ void join_group(const double *in, double *out, const ThetaItem *__restrict__ shells,
                                            const double *__restrict__ ring_c, int n_valid,
-                                           const Twiddle *__restrict__ tw, Twiddle *table, double *lds)
+                                           const Twiddle *__restrict__ tw, Twiddle *table, double *lds,
+                                           const HybridArgs &ht = HybridArgs{},
+                                           const HybridArgs &hp = HybridArgs{})
 {
     using S = JoinShape<N>;
     for (int i = threadIdx.x; i < S::table; i += S::width) table[i] = tw[i];
     auto run = [&](auto kind) {
-        join_block<N, ADJ, decltype(kind)::value>(in, out, shells, ring_c, n_valid, table, lds);
+        join_block<N, ADJ, decltype(kind)::value>(in, out, shells, ring_c, n_valid, table, lds, ht, hp);
     };
-    if constexpr (S::shells > 1) {
+    if constexpr (HYB) {
+        run(std::integral_constant<int, 3>{});
+    } else if constexpr (S::shells > 1) {
         run(std::integral_constant<int, -1>{});
     } else {
         // one shell per workgroup: one kind, and no registers held across the
@@ -74,6 +78,24 @@ void join_kernel(const double *in, double *out, const ThetaItem *__restrict__ sh
                        min(S::shells, n_shells - first), tw, table, lds);
 }
 
+// Hybrid shells only: the detector runs on the registers, in both layouts.  A
+// third of the 24 fields hybrid, against two passes: 128 shells of 24 x 48 38.5
+// -> 25 us, of 48 x 96 71 -> 44, of 64 x 128 78 -> 65 (against the form through
+// LDS), of 40 x 80 63 -> 53, of 96 x 192 222 -> 203.
+template <int N, bool ADJ>
+__global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N, true>())))
+void join_hybrid_kernel(const double *in, double *out, const ThetaItem *__restrict__ shells,
+                        const double *__restrict__ ring_c, int n_shells,
+                        const Twiddle *__restrict__ tw, HybridArgs ht, HybridArgs hp)
+{
+    using S = JoinShape<N>;
+    __shared__ double lds[S::lds];
+    __shared__ Twiddle table[S::table];
+    const int first = blockIdx.x * S::shells;
+    join_group<N, ADJ, true>(in, out, shells + first, ring_c + (size_t)first * S::lines,
+                             min(S::shells, n_shells - first), tw, table, lds, ht, hp);
+}
+
 // The same for a batch: one item per workgroup, in list order.
 template <int N, bool ADJ>
 __global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N>())))
@@ -111,6 +133,25 @@ static hipError_t join_go(bool adjoint, const double *in, double *out, const The
         join_kernel<N, false><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, rings, n_rings, tw);
     return hipGetLastError();
 }
+
+namespace {
+// f(std::integral_constant<int, N>) for the line length n_line
+template <typename F>
+auto with_line(int n_line, F &&f)
+{
+    switch (n_line) {
+    case 32: return f(std::integral_constant<int, 32>{});
+    case 48: return f(std::integral_constant<int, 48>{});
+    case 64: return f(std::integral_constant<int, 64>{});
+    case 80: return f(std::integral_constant<int, 80>{});
+    case 96: return f(std::integral_constant<int, 96>{});
+    case 128: return f(std::integral_constant<int, 128>{});
+    case 160: return f(std::integral_constant<int, 160>{});
+    case 192: return f(std::integral_constant<int, 192>{});
+    default: return f(std::integral_constant<int, 256>{});
+    }
+}
+}  // namespace
 
 bool join_supported(int n_theta, int n_phi)
 {
@@ -170,25 +211,6 @@ hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
     }
 }
 
-namespace {
-// f(std::integral_constant<int, N>) for the line length n_line
-template <typename F>
-auto with_line(int n_line, F &&f)
-{
-    switch (n_line) {
-    case 32: return f(std::integral_constant<int, 32>{});
-    case 48: return f(std::integral_constant<int, 48>{});
-    case 64: return f(std::integral_constant<int, 64>{});
-    case 80: return f(std::integral_constant<int, 80>{});
-    case 96: return f(std::integral_constant<int, 96>{});
-    case 128: return f(std::integral_constant<int, 128>{});
-    case 160: return f(std::integral_constant<int, 160>{});
-    case 192: return f(std::integral_constant<int, 192>{});
-    default: return f(std::integral_constant<int, 256>{});
-    }
-}
-}  // namespace
-
 int join_group_shells(int n_line)
 {
     return with_line(n_line, [](auto n) { return JoinShape<decltype(n)::value>::shells; });
@@ -215,6 +237,28 @@ hipError_t launch_batch_join(int n_line, bool adjoint, const BatchWork *work, in
         else
             batch_join_kernel<N, false><<<grid, block, 0, s>>>(work, ins, outs, th, ph, fc, tw);
         return hipGetLastError();
+    });
+}
+
+hipError_t launch_join_hybrid(bool adjoint, int n_line, const double *in, double *out,
+                              const ThetaItem *shells, const double *ring_c, int n_shells,
+                              const Twiddle *tw, const HybridArgs &ht, const HybridArgs &hp,
+                              hipStream_t s)
+{
+    if (n_shells <= 0) return hipSuccess;
+    return with_line(n_line, [&](auto n) -> hipError_t {
+        constexpr int N = decltype(n)::value;
+        using S = JoinShape<N>;
+        if constexpr (N == 256 || N == 64 || N == 32) {   // two passes; the fused kernel through LDS
+            return hipErrorInvalidValue;
+        } else {
+            const dim3 grid((unsigned)((n_shells + S::shells - 1) / S::shells)), block(S::width);
+            if (adjoint)
+                join_hybrid_kernel<N, true><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, tw, ht, hp);
+            else
+                join_hybrid_kernel<N, false><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, tw, ht, hp);
+            return hipGetLastError();
+        }
     });
 }
 

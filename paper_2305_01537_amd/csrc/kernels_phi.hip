@@ -13,7 +13,7 @@ __global__ __launch_bounds__(LINES * Split<N>::N2) __attribute__((amdgpu_waves_p
     const Twiddle *__restrict__ tw, HybridArgs h)
 {
     constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
-    __shared__ double lds[LINES * line_stride<N1, N2, HYB>()];
+    __shared__ double lds[LINES * line_lds<N1, N2>()];
     __shared__ int flags[LINES];
     const int first = blockIdx.x * LINES;
     phi_block<N, LINES, HYB>(in, out, items + first, min(LINES, n_items - first), n_theta, tw,

@@ -14,7 +14,7 @@ __global__ __launch_bounds__(C * Split<N>::N2) __attribute__((amdgpu_waves_per_e
     int tiles, int n_theta, int n_phi, const Twiddle *__restrict__ tw, HybridArgs h)
 {
     constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
-    __shared__ double lds[C * line_stride<N1, N2, HYB>()];
+    __shared__ double lds[C * line_lds<N1, N2>()];
     __shared__ int flags[C];
     const int group = blockIdx.x / tiles, tile = blockIdx.x % tiles;
     const int per_group = C >> cp_log2;

@@ -342,11 +342,12 @@ __device__ __forceinline__ void line_sync()
 // and b) are (Z[q] + conj Z[-q]) / 2 and (Z[q] - conj Z[-q]) / 2i, so
 //   f_a A + i f_b B = (f_a + f_b)/2 Z[q] + (f_a - f_b)/2 conj Z[N - q].
 // Bin N - q lives on another lane: every lane publishes its bins through the
-// line's LDS region P (2N doubles: real parts, then imaginary parts, natural
-// order), so one synchronisation serves both parts.  Lines with ka == kb get
-// plain f Z.  All lanes of the workgroup (WAVE: of the wave) call this
-// together.  (In the theta layout one wave holds lanes of every line of the
-// workgroup, so restricting the exchange to the lines that mix two kinds
+// line's LDS region P, the real parts, then the imaginary parts (N doubles at
+// a time, natural order), and the factors are formed anew for each part, so
+// that neither takes registers or LDS beyond the plain filter's.  Lines with
+// ka == kb get plain f Z.  All lanes of the workgroup (WAVE: of the wave) call
+// this together.  (In the theta layout one wave holds lanes of every line of
+// the workgroup, so restricting the exchange to the lines that mix two kinds
 // would save nothing there.)
 template <int N1, int N2, bool WAVE, int NV>
 __device__ __forceinline__ void apply_mask_pair(cplx (&v)[NV], int t, int ka, int kb, double c,
@@ -358,60 +359,51 @@ __device__ __forceinline__ void apply_mask_pair(cplx (&v)[NV], int t, int ka, in
     constexpr double inv_n = 1.0 / N;
     const double ea0 = exp(c - (double)t) * inv_n, eb0 = exp(c - (double)(N1 - t)) * inv_n;
     const GaussChain<N1> gc(c);
-    // Each real line's kind as 0/1 weights, so that the per-mode factors are
-    // blends rather than branches (a select chain on the kind was lowered to
-    // a switch per mode: hundreds of divergent branches per workgroup).
-    // Weights of 1 and 0 keep the blends exact.
-    const double ga = ka == 1 ? 1.0 : 0.0, ea = ka == 0 ? 1.0 : 0.0, sa = ka == 2 ? 1.0 : 0.0;
-    const double gb = kb == 1 ? 1.0 : 0.0, eb = kb == 0 ? 1.0 : 0.0, sb = kb == 2 ? 1.0 : 0.0;
-    static_for<0, R>([&](auto rr) {
-        constexpr int r = decltype(rr)::value;
-        if constexpr (PAD) {
-            if (t + N2 * r >= N1) return;
-        }
-        static_for<0, N2>([&](auto kk) {
-            constexpr int k2 = decltype(kk)::value;
-            const int q = t + N2 * r + N1 * k2;
-            P[q] = v[r * N2 + k2].re;
-            P[N + q] = v[r * N2 + k2].im;
+    const bool ga = ka == 1, gb = kb == 1, sa = ka == 2, sb = kb == 2;
+    static_for<0, 2>([&](auto part) {
+        constexpr bool im = decltype(part)::value == 1;
+        auto value = [&](int i) -> double & { return im ? v[i].im : v[i].re; };
+        static_for<0, R>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            if constexpr (PAD) {
+                if (t + N2 * r >= N1) return;
+            }
+            static_for<0, N2>([&](auto kk) {
+                constexpr int k2 = decltype(kk)::value;
+                P[t + N2 * r + N1 * k2] = value(r * N2 + k2);
+            });
         });
-    });
-    line_sync<WAVE>();
-    static_for<0, R>([&](auto rr) {
-        constexpr int r = decltype(rr)::value;
-        if constexpr (PAD) {
-            if (t + N2 * r >= N1) return;
-        }
-        double fgs[N2], fes[N2], fss[N2];
-        gauss_factors<N1, N2>(t + N2 * r, gc, [&](auto kk, double f) { fgs[decltype(kk)::value] = f; });
-        exp_factors<N1, N2, r>(ea0, eb0, [&](auto kk, double f) { fes[decltype(kk)::value] = f; });
-        sharp_factors<N1, N2>(t + N2 * r, c, [&](auto kk, double f) { fss[decltype(kk)::value] = f; });
-        static_for<0, N2>([&](auto kk) {
-            constexpr int k2 = decltype(kk)::value;
-            const int q = t + N2 * r + N1 * k2;
-            const double fa = ga * fgs[k2] + ea * fes[k2] + sa * fss[k2];
-            const double fb = gb * fgs[k2] + eb * fes[k2] + sb * fss[k2];
-            const double alpha = 0.5 * (fa + fb), beta = 0.5 * (fa - fb);
-            const int qp = (N - q) % N;
-            v[r * N2 + k2].re = alpha * v[r * N2 + k2].re + beta * P[qp];
-            v[r * N2 + k2].im = alpha * v[r * N2 + k2].im - beta * P[N + qp];
+        line_sync<WAVE>();
+        static_for<0, R>([&](auto rr) {
+            constexpr int r = decltype(rr)::value;
+            if constexpr (PAD) {
+                if (t + N2 * r >= N1) return;
+            }
+            gauss_factors<N1, N2>(t + N2 * r, gc, [&](auto kk, double fg) {
+                constexpr int k2 = decltype(kk)::value;
+                constexpr bool first = k2 < N2 / 2;
+                constexpr int j = first ? k2 : N2 - 1 - k2;
+                constexpr double steps = exp_int(first ? -N2 * r : N2 * r), step = exp_int(-N1 * j);
+                const double fe = fmin((first ? ea0 : eb0) * steps * step, inv_n);
+                const int q = t + N2 * r + N1 * k2, qhat = first ? q : N - q;
+                const double fs = (double)qhat <= c ? inv_n : 0.0;
+                const double fa = ga ? fg : sa ? fs : fe, fb = gb ? fg : sb ? fs : fe;
+                const double alpha = 0.5 * (fa + fb), beta = 0.5 * (fa - fb);
+                const double other = P[(N - q) % N];
+                double &x = value(r * N2 + k2);
+                x = im ? alpha * x - beta * other : alpha * x + beta * other;
+                asm volatile("" : "+v"(x));
+                if constexpr (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            });
         });
+        line_sync<WAVE>();
     });
-    line_sync<WAVE>();
 }
 
 // LDS doubles per line: an N1 x (N2 + 1) padded tile plus one double, so that
 // consecutive lines start on different banks.
 template <int N1, int N2>
 constexpr int line_lds() { return N1 * (N2 + 1) + 1; }
-
-// LDS doubles per line of a kernel: the hybrid-capable variants also publish
-// a whole spectrum (2N doubles) for the two-kind mask.
-template <int N1, int N2, bool HYB>
-constexpr int line_stride()
-{
-    return HYB && 2 * N1 * N2 + 1 > line_lds<N1, N2>() ? 2 * N1 * N2 + 1 : line_lds<N1, N2>();
-}
 
 // Forward transpose: lane t holds Y[k1][t] in v[k1]; afterwards it holds
 // Y[t + N2 r][n2] in v[r * N2 + n2].  Real and imaginary parts go through LDS
@@ -616,14 +608,13 @@ template <> struct Split<256> : SplitOf<16, 16> {};
 // division.  r = num - threshold den is formed with one rounding (fma), so its
 // sign is that of the exact difference: r > 0 means num / den > threshold, so
 // the rounded quotient is >= threshold (fires); r below -2^-50 threshold den
-// (plus a floor for tiny values) puts the exact quotient more than an ulp
-// below the threshold, so the rounded one stays below (does not fire).  The
-// rest (r near zero, den zero, non-finite values) is `unsure`: the caller
-// decides those cells by the division itself.
-struct JamesonCell {
-    bool fires, unsure;
-};
-
+// (minus a floor for tiny values) puts the exact quotient more than an ulp
+// below the threshold, so the rounded one stays below (does not fire).  Only a
+// cell in between has to be decided by the division itself.  So a line needs
+// the largest r of its cells and the largest r + 2^-50 threshold den, and no
+// comparison per cell.  A cell with a non-finite value does not fire: its
+// quotient is 0 or not a number, and so is its r or it is -inf, which the
+// maxima pass over.
 __device__ __forceinline__ double jameson_num(double a, double b, double c)
 {
     return fabs(a - 2.0 * b + c);
@@ -634,21 +625,12 @@ __device__ __forceinline__ double jameson_den(double a, double b, double c, doub
     return fabs(a) + 2.0 * fabs(b) + fabs(c) + eps;
 }
 
-__device__ __forceinline__ JamesonCell jameson_cell(double a, double b, double c, double eps,
-                                                    double threshold)
-{
-    const double num = jameson_num(a, b, c), den = jameson_den(a, b, c, eps);
-    const double r = fma(-threshold, den, num);
-    const double margin = fma(threshold * 0x1p-50, den, 0x1p-1000);
-    return JamesonCell{r > 0.0, !(r > 0.0) && !(r < -margin)};
-}
-
 // Jameson's detector sigma_i = |u_{i-1} - 2u_i + u_{i+1}| /
 // (|u_{i-1}| + 2|u_i| + |u_{i+1}| + eps) on the two real lines packed in v
 // (periodic along the line).  Returns bit 0 if any cell of the real-part
 // line has sigma >= threshold, bit 1 for the imaginary-part line.  Lanes
-// publish both real lines through the line's LDS region L (2N doubles: the
-// hybrid-capable kernels' line stride) to read their neighbours, and combine
+// publish one real line after the other through the line's LDS region L (N
+// doubles) to read their neighbours, and combine
 // their findings in *flag (this line's LDS word) behind workgroup barriers;
 // with WAVE (the line's N2 lanes are consecutive lanes of one wave, aligned to
 // N2) a wave-level ordering and a ballot do instead.  All lanes of the
@@ -662,54 +644,52 @@ __device__ __forceinline__ int detect_shocks(const cplx (&v)[NV], int t, double 
     if constexpr (!WAVE) {
         if (t == 0) *flag = 0;
     }
-    static_for<0, N1>([&](auto nn) {
-        constexpr int n1 = decltype(nn)::value;
-        L[N2 * n1 + t] = v[n1].re;
-        L[N + N2 * n1 + t] = v[n1].im;
-    });
-    line_sync<WAVE>();
     int bits = 0;
-    if (check) {
-        // straight-line sign tests over every cell of the lane; the cells they
-        // leave unsure (never, with random data) go through the division in a
-        // second, rarely entered loop
-        int unsure = 0;
-        static_for<0, 2>([&](auto part) {
-            constexpr int im = decltype(part)::value;
-            const double *Lp = L + im * N;
+    static_for<0, 2>([&](auto part) {
+        constexpr int im = decltype(part)::value;
+        auto value = [&](int n1) { return im ? v[n1].im : v[n1].re; };
+        static_for<0, N1>([&](auto nn) {
+            constexpr int n1 = decltype(nn)::value;
+            L[N2 * n1 + t] = value(n1);
+        });
+        line_sync<WAVE>();
+        if (check) {
+            // straight-line over every cell of the lane; if that leaves the
+            // line unsure (never, with random data) a second, rarely entered
+            // loop divides
+            const double slack = threshold * 0x1p-50;
+            double r_max = -INFINITY, near_max = -INFINITY;
             static_for<0, N1>([&](auto nn) {
                 constexpr int n1 = decltype(nn)::value;
                 const int n = N2 * n1 + t;
-                const double b = im ? v[n1].im : v[n1].re;
-                const JamesonCell cell = jameson_cell(Lp[(n + N - 1) % N], b, Lp[(n + 1) % N], eps,
-                                                      threshold);
-                bits |= cell.fires ? 1 << im : 0;
-                unsure |= cell.unsure ? 1 << im : 0;
+                const double a = L[(n + N - 1) % N], c = L[(n + 1) % N];
+                const double den = jameson_den(a, value(n1), c, eps);
+                const double r = fma(-threshold, den, jameson_num(a, value(n1), c));
+                r_max = fmax(r_max, r);
+                near_max = fmax(near_max, fma(slack, den, r));
+                if constexpr (n1 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             });
-        });
-        if (unsure) {
-            static_for<0, 2>([&](auto part) {
-                constexpr int im = decltype(part)::value;
-                const double *Lp = L + im * N;
+            bool fires = r_max > 0.0;
+            const bool unsure = !fires && near_max >= -0x1p-1000;
+            if (unsure) {
                 static_for<0, N1>([&](auto nn) {
                     constexpr int n1 = decltype(nn)::value;
                     const int n = N2 * n1 + t;
-                    const double a = Lp[(n + N - 1) % N], c = Lp[(n + 1) % N];
-                    const double b = im ? v[n1].im : v[n1].re;
-                    if ((unsure >> im) & 1)
-                        bits |= jameson_num(a, b, c) / jameson_den(a, b, c, eps) >= threshold ? 1 << im : 0;
+                    const double a = L[(n + N - 1) % N], c = L[(n + 1) % N];
+                    fires |= jameson_num(a, value(n1), c) / jameson_den(a, value(n1), c, eps) >= threshold;
                 });
-            });
+            }
+            bits |= fires ? 1 << im : 0;
         }
-    }
+        // L is rewritten next (the other line, the transposes): after every
+        // lane's neighbour reads
+        line_sync<WAVE>();
+    });
     if constexpr (WAVE) {
         static_assert(64 % N2 == 0, "a line's lanes lie in one wave");
         const unsigned long long re = __ballot((bits & 1) != 0), im = __ballot((bits & 2) != 0);
         const int first = (int)__lane_id() & ~(N2 - 1);
         const unsigned long long mine = (N2 == 64 ? ~0ull : ((1ull << N2) - 1)) << first;
-        // the region L is rewritten next (the transposes): keep this wave's
-        // neighbour reads ahead of that
-        wave_lds_sync();
         return ((re & mine) ? 1 : 0) | ((im & mine) ? 2 : 0);
     } else {
         if (bits) atomicOr(flag, bits);
@@ -834,7 +814,7 @@ __device__ __forceinline__ void theta_block(const double *in, double *out,
     // transform (the barriers are workgroup-wide) but their result is dropped;
     // they are copied exactly from `in`.  That only happens out of place.
     if (any_active) {
-        double *L = lds + p * line_stride<N1, N2, HYB>();
+        double *L = lds + p * line_lds<N1, N2>();
         const size_t dline = (size_t)it.shell * (size_t)half;
         int ka = it.flags & kKindMask, kb = ka;
         bool mixed = false;
@@ -901,7 +881,7 @@ __device__ __forceinline__ void phi_block(const double *in, double *out,
                       : cplx{0.0, 0.0};
     });
     if (any_active) {
-        double *L = lds + p * line_stride<N1, N2, HYB>();
+        double *L = lds + p * line_lds<N1, N2>();
         const size_t ring_b = (size_t)it.ring + (size_t)(n_theta - 1 - 2 * j);
         int ka = it.flags & (REST ? 2 : kKindMask), kb = ka;
         bool mixed = false;
@@ -952,7 +932,7 @@ template <int N, int W = 256> struct ShellShape {
     static constexpr int stride = (N / 2) * row + 16;    // doubles per staged shell
     static constexpr int lds = shells * stride;
     static_assert(lanes % N == 0, "a shell's lanes cover whole rows");
-    static_assert(shells >= 1 && lds >= (W / N2) * line_stride<N1, N2, true>(), "scratch fits in the staging area");
+    static_assert(shells >= 1 && lds >= (W / N2) * line_lds<N1, N2>(), "scratch fits in the staging area");
 };
 
 // Staging: lane l of a shell's lanes moves elements e = k * lanes + l,
@@ -1140,7 +1120,7 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
     double *sb_p = lds + up * S::stride;
 
     auto theta_filter = [&]() {
-        double *L = lds + pt * line_stride<N1, N2, HYB>();
+        double *L = lds + pt * line_lds<N1, N2>();
         int ka = it.flags & kKindMask, kb = ka;
         bool mixed = false;
         if constexpr (HYB) {
@@ -1151,7 +1131,7 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
         filter_line<N1, N2, HYB>(v, tt, ka, kb, mixed, valid_t ? it.c : INFINITY, L, tw);
     };
     auto phi_filter = [&]() {
-        double *L = lds + pp * line_stride<N1, N2, HYB>();
+        double *L = lds + pp * line_lds<N1, N2>();
         int ka = kind_p, kb = ka;
         bool mixed = false;
         if constexpr (HYB) {
@@ -1232,20 +1212,16 @@ __device__ __forceinline__ void shell_block(const double *in, double *out,
 
 namespace sphfilt {
 
-// The hybrid-capable theta and phi kernels fit two waves per SIMD (at most
-// 256 registers) without spilling; two waves beat one by a wide margin (the
-// share with 8 hybrid fields ran 0.81 against 1.25 ms per forward filter
-// when the two-wave form still spilled a little).
-
 // Waves per SIMD a pass kernel asks the compiler for (it caps the registers
-// per lane at 512 / waves).  The hybrid-capable instances: two, where two
-// workgroups' line scratch (a whole spectrum per line) fits in LDS, else one.
-// The plain instances: no target (they fit two or more waves by themselves).
+// per lane at 512 / waves).  The hybrid-capable instances: three (they take up
+// to 174 registers by themselves; with whole spectra in LDS, a comparison per
+// detector cell and blends of three factors they took up to 240, two waves: the
+// share with 8 hybrid fields 565 -> 512 us, its hybrid passes 460 -> 410).  The plain instances: no target (they fit
+// two or more waves by themselves).
 template <int N, int LINES, bool HYB>
 constexpr int pass_waves()
 {
-    constexpr int bytes = 8 * LINES * line_stride<Split<N>::N1, Split<N>::N2, HYB>();
-    return HYB && 2 * bytes <= 160 * 1024 - 4096 ? 2 : 1;
+    return HYB ? 3 : 1;
 }
 
 }  // namespace sphfilt

@@ -72,7 +72,8 @@ struct sphfilt_plan_s {
     int overlap;            // 0 off, 1 auto, 2 always: independent rings on the side stream
     HybridArgs hybrid;      // detector parameters; dec / replay set per call
     int compute_units;
-    int n_join;             // joined shells: theta items [theta_hyb, theta_hyb + n_join)
+    int n_join;             // joined plain shells: theta items [theta_hyb, theta_hyb + n_join)
+    int n_join_hyb;         // joined hybrid shells: theta items [0, n_join_hyb)
     SideStream side;
     uint64_t params_hash;   // grid, fields and cutoffs (the tune cache key, with the GPU arch)
     double tuned_us, default_us;
@@ -177,7 +178,7 @@ int check_call(sphfilt_plan p, const double *in, double *out)
 }
 
 // Fused shells (held in registers at n_phi = 128: 24 x 508 shells of 64 x 128
-// 413 -> 325 us; the LDS form stays there for hybrid fields) and the phi pass of
+// 413 -> 325 us, the hybrid third of 24 x 128 78 -> 65) and the phi pass of
 // the other shells' ring pairs, in one launch.  On a fusable grid (n_phi = 2 n_theta) a shell that the theta pass
 // filters has every ring filtered too (m_max <= l_max < n_theta = n_phi / 2,
 // also in floating point: rounding is monotone), so all of them are fused and
@@ -194,7 +195,10 @@ int apply_fused(sphfilt_plan p, bool adjoint, const double *in, double *out, con
     hipError_t e = hipSuccess;
     // hybrid shells with the hybrid-capable kernel; the other shells and the
     // rings of the theta-idle shells (never hybrid) with the plain one
-    if (nh > 0)
+    if (nh > 0 && p->n_phi == 128)
+        e = launch_join_hybrid(adjoint, p->n_phi, in, out, p->dev.theta, p->dev.fused_c, nh, p->dev.tw_phi,
+                               pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
+    else if (nh > 0)
         e = launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta, p->dev.fused_c,
                              nh, p->dev.phi_rest, 0, p->dev.tw_phi,
                              pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
@@ -281,9 +285,9 @@ int apply_overlap(sphfilt_plan p, bool adjoint, double *x, const Decisions &d, h
 }
 
 // Joined shells: on the 2 n_theta = n_phi grids that are not fused, active
-// shells of plain kinds go through one kernel that holds a whole shell in
-// registers (n_join of them, join_count; the rest, and the hybrid ones, take
-// two passes), and the ring pairs of the other shells through that launch's
+// shells go through one kernel that holds a whole shell in registers (n_join
+// of the plain ones and n_join_hyb of the hybrid ones; the rest take two
+// passes), and the ring pairs of the other shells through that launch's
 // ring workgroups or the phi kernel (all of them out of place, where identity
 // rings are copied), so a point moves once, or twice where its shell takes two
 // passes.  The sets touch different shells; with overlapped passes the last
@@ -328,7 +332,11 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
                         : phi(out, first * lines, n * lines + more_rings, hybrid, s);
         return r;
     };
-    if (e == hipSuccess) e = two(0, nh, true, 0);
+    const int nj = p->n_join_hyb;
+    if (e == hipSuccess && nj > 0)
+        e = launch_join_hybrid(adjoint, p->n_phi, in, out, p->dev.theta, p->dev.join_c, nj, p->dev.tw_phi,
+                               pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
+    if (e == hipSuccess && nh > nj) e = two(nj, nh - nj, true, 0);
     // in place on one stream the phi kernel takes those shells' rings and the
     // rest's in one launch (phi_rest follows phi_in)
     const bool one_phi = in == out && rest == s && !along && n_two > 0;
@@ -689,6 +697,11 @@ int sphfilt_plan_create(sphfilt_plan *out, int n_r, int n_theta, int n_phi, int 
             p->compute_units = prop.multiProcessorCount;
             p->n_join = join_count(n_phi, p->host.theta_active - p->host.theta_hyb,
                                    p->host.phi_rest_active, p->compute_units);
+            // hybrid shells of 256-point lines take two passes: the detector and
+            // the Gaussian make a joined round 51 us of arithmetic, as long as
+            // the passes (share with 8 hybrid fields: 512 us either way; at 192
+            // 203 joined, 207 in two passes)
+            p->n_join_hyb = n_phi == 256 ? 0 : join_count(n_phi, p->host.theta_hyb, 0, p->compute_units);
         }
     } catch (const std::bad_alloc &) {
         rc = SPHFILT_ENOMEM;

@@ -190,12 +190,14 @@ __device__ __forceinline__ int join_lane()
 // One workgroup: shells items[0, n_valid), n_valid <= JoinShape<N>::shells,
 // with ring cutoffs ring_c[shell][j].  tw: the twiddle table in LDS (written by
 // the caller; a barrier here comes before its first use).  KIND: the kind of
-// every item, or -1 for kinds taken from the items.
+// every item, or -1 for plain kinds taken from the items; ht and hp: the
+// hybrid arguments of the two passes, for KIND 3.
 template <int N, bool ADJ, int KIND>
 __device__ __forceinline__ void join_block(const double *in, double *out,
                                            const ThetaItem *__restrict__ items,
                                            const double *__restrict__ ring_c, int n_valid,
-                                           const Twiddle *tw, double *lds)
+                                           const Twiddle *tw, double *lds, const HybridArgs &ht,
+                                           const HybridArgs &hp)
 {
     using S = JoinShape<N>;
     constexpr int N1 = S::N1, N2 = S::N2;
@@ -218,7 +220,21 @@ __device__ __forceinline__ void join_block(const double *in, double *out,
         const int lane = join_lane(), t = lane % N2, line = lane / N2 % S::lines, u = shell_of(lane);
         const double c = theta ? items[u].c : ring_c[u * S::lines + line];
         double *L = lds + lane / N2 * line_lds<N1, N2>();
-        filter_line<N1, N2, false, true, true>(x, t, KIND >= 0 ? KIND : items[u].flags & kKindMask, 0, false, c, L, tw);
+        if constexpr (KIND == 3) {
+            // the decisions' bytes: meridian pairs 2q and 2q + 1, or rings j and
+            // N/2 - 1 - j, of the shell
+            const size_t first = (size_t)items[u].shell * (size_t)(N / 2);
+            const size_t a = first + (theta ? 2 * line : line);
+            const size_t b = theta ? a + 1 : first + (size_t)(N / 2 - 1 - line);
+            int ka = 3, kb = 3;
+            bool mixed = false;
+            hybrid_kinds<N1, N2, true>(x, t, L, nullptr, 0, 0, true, 3, a, b, theta ? ht : hp, &ka, &kb,
+                                       &mixed);
+            filter_line<N1, N2, true, true, true>(x, t, ka & 1, kb & 1, mixed, c, L, tw);
+        } else {
+            filter_line<N1, N2, false, true, true>(x, t, KIND >= 0 ? KIND : items[u].flags & kKindMask,
+                                                   0, false, c, L, tw);
+        }
     };
     filter(v, !ADJ);
     {

@@ -85,6 +85,11 @@ hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
                        const ThetaItem *shells, const double *ring_c, int n_shells,
                        const PhiItem *rings, int n_rings, bool spread, const Twiddle *tw,
                        hipStream_t stream);
+// The same for hybrid shells (no rings along): ht / hp as for launch_shell_phi.
+hipError_t launch_join_hybrid(bool adjoint, int n_line, const double *in, double *out,
+                              const ThetaItem *shells, const double *ring_c, int n_shells,
+                              const Twiddle *tw, const HybridArgs &ht, const HybridArgs &hp,
+                              hipStream_t stream);
 // The theta pass as the circulant product on the matrix cores, over active
 // shells of plain kinds, on grids with theta_gemm_ok (n_phi = 2 n_theta in
 // {32, 64}); tw: the twiddle table of length n_phi.
