@@ -124,6 +124,7 @@ struct sphfilt_batch_s {
     hipEvent_t fork = nullptr, join = nullptr;
     unsigned char *noalloc = nullptr;     // device address of the static scratch array
     int last_noalloc = 0;                 // the last call went through the allocation-free entry
+    int last_work = 1;                    // the last call had items besides joined ones
 };
 
 namespace {
@@ -365,7 +366,7 @@ int effective_wpc(sphfilt_batch b, int wpc)
 // up at once; the kernels still run to their end.
 constexpr int kFaultSpinLimit = 64;
 
-// Enqueue the reset kernel and the persistent kernel(s) of `m` on stream s
+// Enqueue the kernels of one call on stream s
 // (a capture stream, or the caller's stream for the allocation-free call).
 int record(sphfilt_batch b, int mode, int split, int wpc_setting, const CallScratch &sc,
            int wait_fault, hipStream_t s)
@@ -378,11 +379,15 @@ int record(sphfilt_batch b, int mode, int split, int wpc_setting, const CallScra
         return launch_batch(grid, m.d_work + first, n, b->d_patches, sc.ins, sc.outs, b->d_th,
                             b->d_ph, b->d_fc, m.d_shells, sc.counters, m.d_need, ticket, sc.error, deps, spin, bias, b->variant, st);
     };
-    hipError_t e = launch_batch_reset(sc.counters, b->n_shells_total, sc.tickets, 3, sc.error, s);
+    // the work list's tickets and error word and, where items wait for each
+    // other, the shells' counters; joined items use none of them
+    hipError_t e = hipSuccess;
+    if (m.n_work > 0)
+        e = launch_batch_reset(sc.counters, split ? 0 : b->n_shells_total, sc.tickets, 3, sc.error, s);
     for (const JoinClass &c : m.join)
         if (e == hipSuccess)
             e = launch_batch_join(c.n_line, mode & 1, m.d_join + c.first, c.n, sc.ins, sc.outs, b->d_th,
-                                  b->d_ph, b->d_fc, b->d_tw[c.n_line], s);
+                                  b->d_ph, b->d_fc, b->d_tw[c.n_line], b->n_cu, s);
     if (e != hipSuccess) return SPHFILT_EDEVICE;
     if (split == 2 && m.n_indep > 0) {
         // fork: the independent second-pass items on the side stream, the
@@ -540,6 +545,7 @@ int launch(sphfilt_batch b, const double *const *ins, double *const *outs, int a
     rc = get_graph(b, mode, ins, outs, &g);
     if (rc) return rc;
     b->last_noalloc = 0;
+    b->last_work = b->modes[mode].n_work > 0;
     return hipGraphLaunch(g->exec, stream) == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
 }
 
@@ -567,6 +573,7 @@ int launch_noalloc(sphfilt_batch b, const double *const *ins, double *const *out
     if (noalloc_set_pointers(base, ins, outs, (int)b->patches.size(), stream) != hipSuccess)
         return SPHFILT_EDEVICE;
     b->last_noalloc = 1;
+    b->last_work = m.n_work > 0;
     return record(b, mode, b->split, b->wpc, sc, fault("wait") ? 1 : 0, stream);
 }
 
@@ -1110,6 +1117,11 @@ int sphfilt_batch_status(sphfilt_batch batch, int *device_error)
     DeviceGuard g(batch->device);
     if (!g.ok) return SPHFILT_EDEVICE;
     if (hipDeviceSynchronize() != hipSuccess) return SPHFILT_EDEVICE;
+    // joined items flag no error, and a call of only those leaves the word alone
+    if (!batch->last_work) {
+        *device_error = 0;
+        return SPHFILT_OK;
+    }
     // the error word of the last call: the batch's own, or the static array's
     // after an allocation-free call (valid until another such call on the device)
     const int *word = batch->last_noalloc && batch->noalloc

@@ -107,7 +107,8 @@ int batch_blocks_per_cu(int variant);
 // They wait for nothing and nothing waits for them.
 hipError_t launch_batch_join(int n_line, bool adjoint, const BatchWork *work, int n_work,
                              const double *const *ins, double *const *outs, const ThetaItem *th,
-                             const PhiItem *ph, const double *fc, const Twiddle *tw, hipStream_t s);
+                             const PhiItem *ph, const double *fc, const Twiddle *tw,
+                             int compute_units, hipStream_t s);
 // Shells and ring pairs per workgroup of that launch.
 int join_group_shells(int n_line);
 int join_group_rings(int n_line);

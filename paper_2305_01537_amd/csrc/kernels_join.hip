@@ -14,16 +14,23 @@ constexpr int join_waves()
     return N == 256 || (N == 128 && !HYB) ? 4 : 3;
 }
 
-// One workgroup's shells; stages the twiddle table.
+// The twiddle table into LDS, before any use of it.
+template <int N>
+__device__ __forceinline__ void stage_table(const Twiddle *__restrict__ tw, Twiddle *table)
+{
+    for (int i = threadIdx.x; i < JoinShape<N>::table; i += JoinShape<N>::width) table[i] = tw[i];
+    __syncthreads();
+}
+
+// One workgroup's shells, the kind picked for all of them where it can be.
 template <int N, bool ADJ, bool HYB = false>
 __device__ __forceinline__ void join_group(const double *in, double *out, const ThetaItem *__restrict__ shells,
                                            const double *__restrict__ ring_c, int n_valid,
-                                           const Twiddle *__restrict__ tw, Twiddle *table, double *lds,
+                                           const Twiddle *table, double *lds,
                                            const HybridArgs &ht = HybridArgs{},
                                            const HybridArgs &hp = HybridArgs{})
 {
     using S = JoinShape<N>;
-    for (int i = threadIdx.x; i < S::table; i += S::width) table[i] = tw[i];
     auto run = [&](auto kind) {
         join_block<N, ADJ, decltype(kind)::value>(in, out, shells, ring_c, n_valid, table, lds, ht, hp);
     };
@@ -56,26 +63,28 @@ __device__ __forceinline__ void join_group(const double *in, double *out, const 
 template <int N, bool ADJ>
 __global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N>())))
 void join_kernel(const double *in, double *out, const ThetaItem *__restrict__ shells,
-                 const double *__restrict__ ring_c, int n_shells, int shell_groups, int span,
+                 const double *__restrict__ ring_c, int n_shells, int shell_groups, int span, int total,
                  const PhiItem *__restrict__ rings, int n_rings, const Twiddle *__restrict__ tw)
 {
     using S = JoinShape<N>;
     __shared__ double lds[S::lds];
     __shared__ Twiddle table[S::table];
-    // the shell groups are spread evenly over the first `span` workgroups
-    const int b = blockIdx.x;
-    const int group = b < span ? (int)((long long)b * shell_groups / span) : shell_groups;
-    const bool ring = b >= span || (int)((long long)(b + 1) * shell_groups / span) == group;
-    if (ring) {
-        constexpr int LINES = S::width / S::N2;
-        const int first = (b - group) * LINES;
-        phi_block<N, LINES, false, true>(in, out, rings + first, min(LINES, n_rings - first), N / 2, tw, lds,
-                                         nullptr, HybridArgs{}, threadIdx.x);
-        return;
+    stage_table<N>(tw, table);
+    // the shell groups are spread evenly over the first `span` items
+    for (int b = blockIdx.x; b < total; b += gridDim.x) {
+        const int group = b < span ? (int)((long long)b * shell_groups / span) : shell_groups;
+        const bool ring = b >= span || (int)((long long)(b + 1) * shell_groups / span) == group;
+        if (ring) {
+            constexpr int LINES = S::width / S::N2;
+            const int first = (b - group) * LINES;
+            phi_block<N, LINES, false, true>(in, out, rings + first, min(LINES, n_rings - first), N / 2,
+                                             tw, lds, nullptr, HybridArgs{}, join_lane());
+        } else {
+            const int first = group * S::shells;
+            join_group<N, ADJ>(in, out, shells + first, ring_c + (size_t)first * S::lines,
+                               min(S::shells, n_shells - first), table, lds);
+        }
     }
-    const int first = group * S::shells;
-    join_group<N, ADJ>(in, out, shells + first, ring_c + (size_t)first * S::lines,
-                       min(S::shells, n_shells - first), tw, table, lds);
 }
 
 // Hybrid shells only: the detector runs on the registers, in both layouts.  A
@@ -91,46 +100,65 @@ void join_hybrid_kernel(const double *in, double *out, const ThetaItem *__restri
     using S = JoinShape<N>;
     __shared__ double lds[S::lds];
     __shared__ Twiddle table[S::table];
+    stage_table<N>(tw, table);
     const int first = blockIdx.x * S::shells;
     join_group<N, ADJ, true>(in, out, shells + first, ring_c + (size_t)first * S::lines,
-                             min(S::shells, n_shells - first), tw, table, lds, ht, hp);
+                             min(S::shells, n_shells - first), table, lds, ht, hp);
 }
 
-// The same for a batch: one item per workgroup, in list order.
+// The same for a batch, over its list of items.
 template <int N, bool ADJ>
 __global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N>())))
-void batch_join_kernel(const BatchWork *__restrict__ work, const double *const *ins, double *const *outs,
+void batch_join_kernel(const BatchWork *__restrict__ work, int n_work, const double *const *ins, double *const *outs,
                        const ThetaItem *__restrict__ th, const PhiItem *__restrict__ ph,
                        const double *__restrict__ fc, const Twiddle *__restrict__ tw)
 {
     using S = JoinShape<N>;
     __shared__ double lds[S::lds];
     __shared__ Twiddle table[S::table];
-    const BatchWork w = work[blockIdx.x];
-    const double *in = ins[w.patch];
-    double *out = outs[w.patch];
-    if (w.pass == 1)
-        phi_block<N, S::width / S::N2, false, true>(in, out, ph + w.first, w.n_valid, N / 2, tw, lds,
-                                                    nullptr, HybridArgs{}, threadIdx.x);
-    else
-        join_group<N, ADJ>(in, out, th + w.first, fc + w.aux, w.n_valid, tw, table, lds);
+    stage_table<N>(tw, table);
+    for (int k = blockIdx.x; k < n_work; k += gridDim.x) {
+        const BatchWork w = work[k];
+        const double *in = ins[w.patch];
+        double *out = outs[w.patch];
+        if (w.pass == 1)
+            phi_block<N, S::width / S::N2, false, true>(in, out, ph + w.first, w.n_valid, N / 2, tw, lds,
+                                                        nullptr, HybridArgs{}, join_lane());
+        else
+            join_group<N, ADJ>(in, out, th + w.first, fc + w.aux, w.n_valid, table, lds);
+    }
+}
+
+// Workgroups of a launch over `total` items.  One per item, except where one
+// workgroup fills a compute unit and every unit gets eight items or more: then
+// one per unit, which takes every grid-th item.  Its waves go on to the next
+// item's loads as they finish their own part of the last, which a new
+// workgroup cannot do before all of them have (6144 shells of 128 x 256, all
+// filtered, 787 -> 737 us forward, 831 -> 744 adjoint; 3840 of 80 x 160 261 ->
+// 229; 3072 of 96 x 192 265 -> 233).  With fewer items the units end unevenly
+// (1024 items: 95.6 -> 100.5 us; 1362: 154 -> 155).
+template <int N>
+static unsigned join_grid(int total, int compute_units)
+{
+    return (unsigned)(N >= 160 && compute_units > 0 && total >= 8 * compute_units ? compute_units : total);
 }
 
 template <int N>
 static hipError_t join_go(bool adjoint, const double *in, double *out, const ThetaItem *shells,
                           const double *ring_c, int n_shells, const PhiItem *rings, int n_rings,
-                          bool spread, const Twiddle *tw, hipStream_t s)
+                          int compute_units, const Twiddle *tw, hipStream_t s)
 {
     using S = JoinShape<N>;
     constexpr int LINES = S::width / S::N2;
     const int groups = (n_shells + S::shells - 1) / S::shells;
     const int ring_groups = (n_rings + LINES - 1) / LINES;
-    const dim3 grid((unsigned)(groups + ring_groups)), block(S::width);
-    const int span = groups + (spread ? ring_groups * 4 / 5 : 0);
+    const int total = groups + ring_groups;
+    const dim3 grid(join_grid<N>(total, compute_units)), block(S::width);
+    const int span = groups + (join_spread(N, n_rings, compute_units) ? ring_groups * 4 / 5 : 0);
     if (adjoint)
-        join_kernel<N, true><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, rings, n_rings, tw);
+        join_kernel<N, true><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, total, rings, n_rings, tw);
     else
-        join_kernel<N, false><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, rings, n_rings, tw);
+        join_kernel<N, false><<<grid, block, 0, s>>>(in, out, shells, ring_c, n_shells, groups, span, total, rings, n_rings, tw);
     return hipGetLastError();
 }
 
@@ -195,18 +223,18 @@ bool join_spread(int n_line, int n_rings, int compute_units)
 
 hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
                        const ThetaItem *shells, const double *ring_c, int n_shells,
-                       const PhiItem *rings, int n_rings, bool spread, const Twiddle *tw, hipStream_t s)
+                       const PhiItem *rings, int n_rings, int compute_units, const Twiddle *tw, hipStream_t s)
 {
     if (n_shells < 0 || n_rings < 0) return hipErrorInvalidValue;
     if (n_shells + n_rings == 0) return hipSuccess;
     switch (n_line) {
-    case 48: return join_go<48>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
-    case 80: return join_go<80>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
-    case 96: return join_go<96>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
-    case 128: return join_go<128>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
-    case 160: return join_go<160>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
-    case 192: return join_go<192>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
-    case 256: return join_go<256>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, spread, tw, s);
+    case 48: return join_go<48>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
+    case 80: return join_go<80>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
+    case 96: return join_go<96>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
+    case 128: return join_go<128>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
+    case 160: return join_go<160>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
+    case 192: return join_go<192>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
+    case 256: return join_go<256>(adjoint, in, out, shells, ring_c, n_shells, rings, n_rings, compute_units, tw, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -226,16 +254,17 @@ int join_group_rings(int n_line)
 
 hipError_t launch_batch_join(int n_line, bool adjoint, const BatchWork *work, int n_work,
                              const double *const *ins, double *const *outs, const ThetaItem *th,
-                             const PhiItem *ph, const double *fc, const Twiddle *tw, hipStream_t s)
+                             const PhiItem *ph, const double *fc, const Twiddle *tw,
+                             int compute_units, hipStream_t s)
 {
     if (n_work <= 0) return hipSuccess;
     return with_line(n_line, [&](auto n) {
         constexpr int N = decltype(n)::value;
-        const dim3 grid((unsigned)n_work), block(JoinShape<N>::width);
+        const dim3 grid(join_grid<N>(n_work, compute_units)), block(JoinShape<N>::width);
         if (adjoint)
-            batch_join_kernel<N, true><<<grid, block, 0, s>>>(work, ins, outs, th, ph, fc, tw);
+            batch_join_kernel<N, true><<<grid, block, 0, s>>>(work, n_work, ins, outs, th, ph, fc, tw);
         else
-            batch_join_kernel<N, false><<<grid, block, 0, s>>>(work, ins, outs, th, ph, fc, tw);
+            batch_join_kernel<N, false><<<grid, block, 0, s>>>(work, n_work, ins, outs, th, ph, fc, tw);
         return hipGetLastError();
     });
 }

@@ -206,7 +206,7 @@ int apply_fused(sphfilt_plan p, bool adjoint, const double *in, double *out, con
         e = p->n_phi == 128
                 ? launch_join(adjoint, p->n_phi, in, out, p->dev.theta + nh,
                               p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh, p->dev.phi_rest,
-                              n_rings, false, p->dev.tw_phi, s)
+                              n_rings, 0, p->dev.tw_phi, s)
                 : launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta + nh,
                                    p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh,
                                    p->dev.phi_rest, n_rings, p->dev.tw_phi,
@@ -321,7 +321,7 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
     auto join = [&](int n, int n_rings, hipStream_t st) {
         return launch_join(adjoint, p->n_phi, in, out, p->dev.theta + nh,
                            p->dev.join_c + (size_t)nh * lines, n, p->dev.phi_rest, n_rings,
-                           join_spread(p->n_phi, n_rings, p->compute_units), p->dev.tw_phi, st);
+                           p->compute_units, p->dev.tw_phi, st);
     };
     // two passes of shells [first, first + n), whose rings are phi_in's
     auto two = [&](int first, int n, bool hybrid, int more_rings) {

@@ -188,8 +188,9 @@ __device__ __forceinline__ int join_lane()
 }
 
 // One workgroup: shells items[0, n_valid), n_valid <= JoinShape<N>::shells,
-// with ring cutoffs ring_c[shell][j].  tw: the twiddle table in LDS (written by
-// the caller; a barrier here comes before its first use).  KIND: the kind of
+// with ring cutoffs ring_c[shell][j].  tw: the twiddle table in LDS.  A wave
+// may start on its next item when it is done: until that item's exchange, which
+// begins with a barrier, it only touches its own lines' scratch.  KIND: the kind of
 // every item, or -1 for plain kinds taken from the items; ht and hp: the
 // hybrid arguments of the two passes, for KIND 3.
 template <int N, bool ADJ, int KIND>
@@ -215,7 +216,6 @@ __device__ __forceinline__ void join_block(const double *in, double *out,
         else
             join_theta_hbm<N, true>(src, nullptr, v, t, line, sign(u));
     }
-    __syncthreads();                                                 // the twiddle table
     auto filter = [&](cplx (&x)[Split<N>::NV], bool theta) {
         const int lane = join_lane(), t = lane % N2, line = lane / N2 % S::lines, u = shell_of(lane);
         const double c = theta ? items[u].c : ring_c[u * S::lines + line];

@@ -74,7 +74,7 @@ hipError_t launch_shell_phi(bool adjoint, int n_theta, int n_phi, const double *
 // which is filtered, each held in one workgroup's registers, and in the same
 // launch the phi pass of n_rings ring pairs of shells that the theta pass
 // leaves alone; ring_c and tw as for launch_shell_phi, n_line = n_phi =
-// 2 n_theta.  spread: the shells among the ring workgroups, not before them.
+// 2 n_theta.  compute_units: of the device, for the launch shape.
 // join_supported: the grids that are not shell_fusable (n_phi = 128 is both).
 bool join_supported(int n_theta, int n_phi);
 // How many of n shells to join, in a launch with n_rings ring pairs; the others
@@ -83,7 +83,7 @@ int join_count(int n_line, int n, int n_rings, int compute_units);
 bool join_spread(int n_line, int n_rings, int compute_units);
 hipError_t launch_join(bool adjoint, int n_line, const double *in, double *out,
                        const ThetaItem *shells, const double *ring_c, int n_shells,
-                       const PhiItem *rings, int n_rings, bool spread, const Twiddle *tw,
+                       const PhiItem *rings, int n_rings, int compute_units, const Twiddle *tw,
                        hipStream_t stream);
 // The same for hybrid shells (no rings along): ht / hp as for launch_shell_phi.
 hipError_t launch_join_hybrid(bool adjoint, int n_line, const double *in, double *out,
