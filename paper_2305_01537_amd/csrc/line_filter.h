@@ -716,6 +716,9 @@ __device__ __forceinline__ void hybrid_kinds(const cplx (&v)[NV], int t, double 
     *mixed = false;
     if (!h.present) return;
     const bool hybrid = active && kind == 3;
+    if constexpr (WAVE) {
+        if (!__any(hybrid)) return;              // a wave of plain lines
+    }
     int bits = 0;
     if (h.replay) {
         if (hybrid) bits = (h.dec[dec_a] ? 1 : 0) | (h.dec[dec_b] ? 2 : 0);
@@ -818,9 +821,14 @@ __device__ __forceinline__ void theta_block(const double *in, double *out,
         const size_t dline = (size_t)it.shell * (size_t)half;
         int ka = it.flags & kKindMask, kb = ka;
         bool mixed = false;
-        if constexpr (HYB)
-            hybrid_kinds<N1, N2, false>(v, t, L, flags, p, C, active, ka, dline + kr, dline + ki, h,
-                                        &ka, &kb, &mixed);
+        if constexpr (HYB) {
+            // a workgroup of plain shells (uniform) has nothing to detect
+            bool any_hybrid = false;
+            for (int i = 0; i < n_valid; ++i) any_hybrid |= (items[i].flags & kKindMask) == 3;
+            if (any_hybrid)
+                hybrid_kinds<N1, N2, false>(v, t, L, flags, p, C, active, ka, dline + kr, dline + ki, h,
+                                            &ka, &kb, &mixed);
+        }
         filter_line<N1, N2, HYB>(v, t, ka, kb, mixed, active ? it.c : INFINITY, L, tw);
     }
     if (valid && (active || !any_active)) {

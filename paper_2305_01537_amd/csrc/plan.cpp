@@ -102,7 +102,7 @@ struct Decisions {
 };
 
 // Hybrid arguments of one launch: the decision buffer of its pass, and
-// `present` only for the launch over hybrid items (the hybrid-capable kernel
+// `present` only for a launch with hybrid items (the hybrid-capable kernel
 // instance costs registers and occupancy the plain one does not).
 HybridArgs pass_args(const sphfilt_plan p, unsigned char *dec, const Decisions &d, bool hybrid)
 {
@@ -114,14 +114,18 @@ HybridArgs pass_args(const sphfilt_plan p, unsigned char *dec, const Decisions &
 }
 
 // The theta pass (or the phi pass) over items [0, n) of a list whose first
-// n_hyb items are hybrid: those with the hybrid-capable kernel, the rest with
-// the plain one.
-// With the circulant variant the plain active items [n_hyb, n_active) go to
-// the matrix-core kernel (the item lists put the active items first).
+// n_hyb items are hybrid.  With hybrid items among them all go to the
+// hybrid-capable kernel in one launch: it runs plain lines about as fast as the
+// plain one (its workgroups of plain shells skip the detector), and a second
+// launch costs more than that (a third of the fields hybrid: 5 x 37 shells of
+// 48 x 128 32 us in two launches a pass, 21 in one; 20 x 148 74 / 59; 24 x 256
+// of 64 x 256 266 / 257).  With the circulant variant the plain active items
+// [n_hyb, n_active) go to the matrix-core kernel instead (the item lists put the
+// active items first).
 hipError_t theta_split(sphfilt_plan p, const double *in, double *out, const ThetaItem *items, int n,
                        int n_hyb, const Decisions &d, hipStream_t s)
 {
-    const int nh = n_hyb < n ? n_hyb : n;
+    const int nh = n_hyb == 0 ? 0 : n_hyb < n && p->theta_mfma ? n_hyb : n;
     hipError_t e = hipSuccess;
     if (nh > 0)
         e = launch_theta(2 * p->n_theta, p->theta_cols, in, out, items, nh, p->n_theta, p->n_phi,
@@ -143,14 +147,8 @@ hipError_t theta_split(sphfilt_plan p, const double *in, double *out, const Thet
 hipError_t phi_split(sphfilt_plan p, const double *in, double *out, const PhiItem *items, int n,
                      int n_hyb, const Decisions &d, hipStream_t s)
 {
-    const int nh = n_hyb < n ? n_hyb : n;
-    hipError_t e = hipSuccess;
-    if (nh > 0)
-        e = launch_phi(p->n_phi, p->phi_lines, in, out, items, nh, p->n_theta, p->dev.tw_phi, pass_args(p, d.phi, d, true), s);
-    if (e == hipSuccess && n > nh)
-        e = launch_phi(p->n_phi, p->phi_lines, in, out, items + nh, n - nh, p->n_theta,
-                       p->dev.tw_phi, pass_args(p, d.phi, d, false), s);
-    return e;
+    return launch_phi(p->n_phi, p->phi_lines, in, out, items, n, p->n_theta, p->dev.tw_phi,
+                      pass_args(p, d.phi, d, n_hyb > 0), s);
 }
 
 int run_pass(sphfilt_plan p, Pass which, const double *in, double *out, bool all_items,
@@ -191,18 +189,26 @@ int apply_fused(sphfilt_plan p, bool adjoint, const double *in, double *out, con
     const HostTables &t = p->host;
     if (t.theta_active != t.n_fused) return SPHFILT_EUNSUPPORTED;
     const int n_rings = in == out ? t.phi_rest_active : (int)t.phi_rest.size();
-    const int nh = t.fused_hyb, lines = p->n_theta / 2;
+    // With hybrid shells among them, up to 128 MiB of shells go through the
+    // hybrid-capable kernel in one launch with the rings (a third of the fields
+    // hybrid: 5 x 37 shells of 32 x 64 17.1 us in two launches, 11.6 in one; 24 x
+    // 128 24.3 / 19.0; but 24 x 1024, 400 MB, 204 / 210: its workgroups are
+    // larger and hold more registers).  At n_phi = 128 both kinds are joined.
+    const bool together = t.fused_hyb > 0 && p->n_phi != 128 && !p->theta_mfma &&
+                          8LL * t.n_fused * p->n_theta * p->n_phi <= 128LL << 20;
+    const int nh = together ? t.n_fused : t.fused_hyb, lines = p->n_theta / 2;
+    const int rings_h = together ? n_rings : 0;
     hipError_t e = hipSuccess;
-    // hybrid shells with the hybrid-capable kernel; the other shells and the
+    // else hybrid shells with the hybrid-capable kernel; the other shells and the
     // rings of the theta-idle shells (never hybrid) with the plain one
     if (nh > 0 && p->n_phi == 128)
         e = launch_join_hybrid(adjoint, p->n_phi, in, out, p->dev.theta, p->dev.fused_c, nh, p->dev.tw_phi,
                                pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
     else if (nh > 0)
         e = launch_shell_phi(adjoint, p->n_theta, p->n_phi, in, out, p->dev.theta, p->dev.fused_c,
-                             nh, p->dev.phi_rest, 0, p->dev.tw_phi,
+                             nh, p->dev.phi_rest, rings_h, p->dev.tw_phi,
                              pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
-    if (e == hipSuccess && (t.n_fused > nh || n_rings > 0))
+    if (e == hipSuccess && (t.n_fused > nh || n_rings > rings_h))
         e = p->n_phi == 128
                 ? launch_join(adjoint, p->n_phi, in, out, p->dev.theta + nh,
                               p->dev.fused_c + (size_t)nh * lines, t.n_fused - nh, p->dev.phi_rest,
@@ -336,11 +342,15 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
     if (e == hipSuccess && nj > 0)
         e = launch_join_hybrid(adjoint, p->n_phi, in, out, p->dev.theta, p->dev.join_c, nj, p->dev.tw_phi,
                                pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
-    if (e == hipSuccess && nh > nj) e = two(nj, nh - nj, true, 0);
-    // in place on one stream the phi kernel takes those shells' rings and the
-    // rest's in one launch (phi_rest follows phi_in)
+    // in place on one stream the phi kernel takes the two-pass shells' rings and
+    // the rest's in one launch (phi_rest follows phi_in); where no plain shell
+    // is joined, hybrid and plain shells share the launches
+    const bool one_two = n_join == 0 && nh > nj && n_two > 0;
     const bool one_phi = in == out && rest == s && !along && n_two > 0;
-    if (e == hipSuccess) e = two(done, n_two, false, one_phi ? n_rest : 0);
+    if (e == hipSuccess && nh > nj && !one_two) e = two(nj, nh - nj, true, 0);
+    if (e == hipSuccess)
+        e = one_two ? two(nj, t.theta_active - nj, true, one_phi ? n_rest : 0)
+                    : two(done, n_two, false, one_phi ? n_rest : 0);
     if (e == hipSuccess && n_join > 0) e = join(n_join, along && rest == s ? n_rest : 0, s);
     if (e == hipSuccess && along && rest != s) e = join(0, n_rest, rest);
     if (e == hipSuccess && !along && !one_phi)
