@@ -28,6 +28,15 @@ def _aligned(t: torch.Tensor) -> torch.Tensor:
     return t if t.data_ptr() % 16 == 0 else t.clone()
 
 
+def _decisions(plan: Plan, device):
+    """Decision buffers that nothing but the replay reads: every hybrid line's
+    byte is written by the forward, and no other byte is looked at, so they
+    need no zeroing launches (unlike plan.decision_buffers())."""
+    F, R, T, P = plan.shape
+    return (torch.empty((F, R, P // 2), dtype=torch.uint8, device=device),
+            torch.empty((F, R, T), dtype=torch.uint8, device=device))
+
+
 class SphFilter(torch.autograd.Function):
     """y = F x on the GPU; the backward applies F^T through the adjoint kernels."""
 
@@ -36,7 +45,7 @@ class SphFilter(torch.autograd.Function):
         ctx.plan = plan
         x = _aligned(x)
         if plan.has_hybrid:
-            th, ph = plan.decision_buffers(x.device)
+            th, ph = _decisions(plan, x.device)
             y = plan.apply_ex(x, theta_dec=th, phi_dec=ph, replay=False)
             ctx.save_for_backward(th, ph)
             return y
