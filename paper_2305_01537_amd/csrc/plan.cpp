@@ -362,6 +362,31 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
     return e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
 }
 
+// Out of place, forward: the rings of shells that the theta pass leaves alone
+// straight from `in`, instead of a copy by the theta pass that the phi pass
+// reads and writes again.  It takes a third launch, which pays from about 100 MB
+// of saved traffic on (32 bytes per point of such a ring that is filtered): 144
+// MB saved 471 -> 373 us (24 x 256 shells of 128 x 160 at cal-L = 3), 219 MB 132 ->
+// 103, 586 MB 409 -> 308, but 55 MB 34 -> 43 and 48 MB 68 -> 72.  (The adjoint's
+// first pass reads every ring once as it is.)
+constexpr long long kDirectMinBytes = 96LL << 20;
+
+bool rings_direct(const sphfilt_plan p)
+{
+    return !p->theta_mfma && 32LL * p->host.phi_rest_active * p->n_phi >= kDirectMinBytes;
+}
+
+int apply_direct(sphfilt_plan p, const double *in, double *out, const Decisions &d, hipStream_t s)
+{
+    const HostTables &t = p->host;
+    hipError_t e = theta_split(p, in, out, p->dev.theta, t.theta_active, t.theta_hyb, d, s);
+    const int n_in = (int)t.phi_in.size();
+    // the same kernel instance for all rings as in place
+    if (e == hipSuccess) e = phi_split(p, out, out, p->dev.phi_in, n_in, t.phi_hyb, d, s);
+    if (e == hipSuccess) e = phi_split(p, in, out, p->dev.phi_rest, (int)t.phi_rest.size(), t.phi_hyb, d, s);
+    return e == hipSuccess ? SPHFILT_OK : SPHFILT_EDEVICE;
+}
+
 // Two passes in the given order.  Out of place, the first pass runs over all
 // items (copying identity lines) and the second works in place on `out`.
 int apply_two(sphfilt_plan p, Pass first, Pass second, const double *in, double *out,
@@ -382,6 +407,7 @@ int apply_two(sphfilt_plan p, Pass first, Pass second, const double *in, double 
         if (rc != SPHFILT_EUNSUPPORTED) return rc;
     }
     const bool inplace = in == out;
+    if (!inplace && first == Pass::Theta && rings_direct(p)) return apply_direct(p, in, out, d, s);
     rc = run_pass(p, first, in, out, !inplace, d, s);
     if (rc) return rc;
     return run_pass(p, second, out, out, false, d, s);
