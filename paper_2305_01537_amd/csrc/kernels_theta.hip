@@ -13,8 +13,7 @@ __global__ __launch_bounds__(C * Split<N>::N2) __attribute__((amdgpu_waves_per_e
     const double *in, double *out, const ThetaItem *__restrict__ items, int n_items, int cp_log2,
     int tiles, int n_theta, int n_phi, const Twiddle *__restrict__ tw, HybridArgs h)
 {
-    constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
-    __shared__ double lds[C * line_lds<N1, N2>()];
+    __shared__ double lds[pass_lds<N, C, HYB, true>()];
     __shared__ int flags[C];
     const int group = blockIdx.x / tiles, tile = blockIdx.x % tiles;
     const int per_group = C >> cp_log2;

@@ -865,7 +865,7 @@ __device__ __forceinline__ void theta_block(const double *in, double *out,
 // or hybrid shell is never left alone): the Gaussian's code and registers are
 // left out, and the line filter holds as few registers as it can.
 // ---------------------------------------------------------------------------
-template <int N, int LINES, bool HYB, bool REST = false>
+template <int N, int LINES, bool HYB, bool REST = false, bool TOGETHER = false>
 __device__ __forceinline__ void phi_block(const double *in, double *out,
                                           const PhiItem *__restrict__ items, int n_valid,
                                           int n_theta, const Twiddle *__restrict__ tw, double *lds, int *flags, const HybridArgs &h, int lane)
@@ -888,6 +888,7 @@ __device__ __forceinline__ void phi_block(const double *in, double *out,
         v[n1] = valid ? cplx{ld_piece<cached>(in + a + N2 * n1 + t), ld_piece<cached>(in + b + N2 * n1 + t)}
                       : cplx{0.0, 0.0};
     });
+    if constexpr (TOGETHER) __syncthreads();   // see phi_kernel
     if (any_active) {
         double *L = lds + p * line_lds<N1, N2>();
         const size_t ring_b = (size_t)it.ring + (size_t)(n_theta - 1 - 2 * j);
@@ -1230,6 +1231,31 @@ template <int N, int LINES, bool HYB>
 constexpr int pass_waves()
 {
     return HYB ? 3 : 1;
+}
+
+// LDS doubles of a pass kernel's workgroup (LINES lines).  Beyond what its
+// lines need, the plain instances below reserve so much that a compute unit
+// holds at most `units` waves: their accesses cover only parts of 128-byte
+// lines (64-byte ring pieces; theta tiles whose rows start inside a line), and
+// with more waves in flight the other parts leave the cache before they are
+// used.  Dense, 800 MB, waves limited by registers / so: theta 48 points 496 /
+// 430 us at 8 waves (464 at 10, 427 at 6), 80 points 442 / 424 at 12 (440 at
+// 16, 459 at 8); phi 64 points 304 / 288 at 12 (292 at 16, 294 at 9), 96 points
+// 317 / 308 at 10 (309 at 8).  The other lengths measured no faster.
+template <int N, int LINES, bool HYB, bool THETA>
+constexpr int pass_lds()
+{
+    constexpr int need = LINES * line_lds<Split<N>::N1, Split<N>::N2>();
+    constexpr int units = HYB ? 0 : THETA ? (N == 48 ? 8 : N == 80 ? 12 : 0) : (N == 64 ? 12 : N == 96 ? 10 : 0);
+    if constexpr (units == 0) {
+        return need;
+    } else {
+        constexpr int waves = (LINES * Split<N>::N2 + 63) / 64;
+        constexpr int all = 160 * 1024 - 4096;            // flags and granularity beside it
+        constexpr int part = all / units * waves / 8;
+        constexpr int most = 60 * 1024 / 8;               // a static array's limit is 64 KB
+        return need > part ? need : part < most ? part : most > need ? most : need;
+    }
 }
 
 }  // namespace sphfilt

@@ -658,8 +658,8 @@ int tune_plan(sphfilt_plan p, const std::string &arch, const char *cache_path)
 }
 
 // A plan's default ring pairs per phi workgroup: the fastest measured for
-// the phi pass alone on dense MI355X grids (smaller workgroups hold fewer
-// waves at each barrier and drain more evenly): 4 at n_phi = 256 (265
+// the phi pass alone on dense MI355X grids (smaller workgroups drain
+// more evenly): 4 at n_phi = 256 (265
 // against 270 us for 16), 8 at 64, 80, 96, 128, 160 and 192 (1-4 % faster
 // than a full 256-lane workgroup); a full workgroup at 32 and 48, where that
 // is fastest.  The batch kernels keep full workgroups.
