@@ -286,7 +286,9 @@ __device__ __forceinline__ void apply_mask(cplx (&v)[NV], int t, int kind, doubl
 
 // The same for lines that are exponential or sharp, without a branch on the
 // kind (whose phis hold registers): 1/N up to the cutoff, above it the
-// exponential or nothing.
+// exponential or nothing.  |q| <= c is decided as |q| <= floor(c): c - b rounds
+// where c is small against b, and a sharp line's cutoff just below an integer
+// must not pass as that integer; floor(c) - b is exact.
 template <int N1, int N2, int NV>
 __device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp, double c)
 {
@@ -296,8 +298,9 @@ __device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp,
     static_for<0, 2>([&](auto hh) {
         constexpr int h = decltype(hh)::value;
         // the sequences of exp_factors: |q| = b -+ N2 r + N1 j
-        const double room = c - (double)(h == 0 ? t : N1 - t);
-        const double e = sharp ? 0.0 : exp(room) * inv_n;
+        const double b = (double)(h == 0 ? t : N1 - t);
+        const double room = floor(c) - b;
+        const double e = sharp ? 0.0 : exp(c - b) * inv_n;
         static_for<0, R>([&](auto rr) {
             constexpr int r = decltype(rr)::value;
             if constexpr (PAD) {
