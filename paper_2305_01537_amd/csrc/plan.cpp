@@ -368,12 +368,14 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
 // of saved traffic on (32 bytes per point of such a ring that is filtered): 144
 // MB saved 471 -> 373 us (24 x 256 shells of 128 x 160 at cal-L = 3), 219 MB 132 ->
 // 103, 586 MB 409 -> 308, but 55 MB 34 -> 43 and 48 MB 68 -> 72.  (The adjoint's
-// first pass reads every ring once as it is.)
+// first pass reads every ring once as it is.)  Not on grids with fused shells
+// (reached there with fusing off): phi_in leaves the rings of fused shells out.
 constexpr long long kDirectMinBytes = 96LL << 20;
 
 bool rings_direct(const sphfilt_plan p)
 {
-    return !p->theta_mfma && 32LL * p->host.phi_rest_active * p->n_phi >= kDirectMinBytes;
+    return p->host.n_fused == 0 && !p->theta_mfma &&
+           32LL * p->host.phi_rest_active * p->n_phi >= kDirectMinBytes;
 }
 
 int apply_direct(sphfilt_plan p, const double *in, double *out, const Decisions &d, hipStream_t s)

@@ -219,3 +219,60 @@ def test_rings_straight_from_the_input_out_of_place(torch_gpu, kind):
     for f in range(6):
         assert rel(got[f].cpu().numpy(), ref[f]) <= TOL, f
     plan.close()
+
+
+@pytest.mark.parametrize("shape,L,hybrid", [((24, 256, 64, 128), 1.0, False), ((24, 256, 64, 128), 1.0, True),
+                                            ((24, 3600, 16, 32), 0.012, False), ((24, 1200, 32, 64), 0.18, True),
+                                            ((8, 256, 96, 192), 1.0, False), ((10, 256, 96, 192), 1.0, True)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_two_passes_out_of_place_filter_every_ring(torch_gpu, shape, L, hybrid):
+    """With fusing off, on grids that are fused or joined otherwise and where the
+    rings of theta-idle shells move 96 MiB or more: the call out of place gives
+    the bits of the call in place and the oracle's filter, and every byte of a
+    hybrid field's decisions is written."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.autograd import sph_filter
+    from paper_2305_01537_amd.filter import Plan
+    F, R, T, P = shape
+    rng = np.random.default_rng(641)
+    x = rng.standard_normal(shape)
+    parity = np.where(np.arange(F) % 2 == 0, 1, -1).astype(np.int32)
+    kind = np.where(np.arange(F) % 3 == 1, SHARP, EXP).astype(np.int32)
+    if hybrid:
+        kind[:2] = HYBRID
+    plan = Plan(R, T, P, F, parity=parity, L=L, kind=kind)
+    plan.set_fused(False)
+    st = plan.stats()
+    idle = st["phi_rings_active"] - st["theta_shells_active"] * T
+    print(f"[gpu] two passes {shape} hybrid={hybrid}: {idle} rings of idle shells", flush=True)
+    assert 32 * (idle // 2) * P >= 96 << 20
+    xd = torch.from_numpy(x).cuda()
+    want = plan.apply(xd.clone(), out=None)
+    inplace = xd.clone()
+    plan.apply(inplace, out=inplace)
+    assert torch.equal(want, inplace)
+    shells = [0, 1, R // 8, R // 4, R // 2, R - 1]
+    rho = synth.uniform_rho(R)[shells]
+    for f in (0, 1, F - 1):
+        ref = oracle.forward(x[f:f + 1, shells], parity=parity[f:f + 1], L=np.full(1, L), rho=rho,
+                             kind=kind[f:f + 1])
+        got = want[f, shells].cpu().numpy()
+        assert rel(got, ref[0]) <= TOL, (f, rel(got, ref[0]))
+    if hybrid:
+        dec = [torch.full(s, 255, dtype=torch.uint8, device="cuda") for s in ((F, R, P // 2), (F, R, T))]
+        mine = [d.clone() for d in dec]
+        plan.apply_ex(xd, theta_dec=dec[0], phi_dec=dec[1])
+        y = xd.clone()
+        plan.apply_ex(y, out=y, theta_dec=mine[0], phi_dec=mine[1])
+        for a, b in zip(dec, mine):
+            assert int(a[:2].max()) <= 1 and torch.equal(a, b)
+        del a, b, y
+        g = torch.from_numpy(rng.standard_normal(shape)).cuda()
+        gref = plan.apply_ex(g, adjoint=True, theta_dec=dec[0], phi_dec=dec[1], replay=True)
+        del dec, mine                       # their 255s are what the next empty buffers hold
+        xd.requires_grad_(True)
+        out = sph_filter(xd, plan)
+        assert torch.equal(out.detach(), want)
+        out.backward(g)
+        assert torch.equal(xd.grad, gref)
+    plan.close()
