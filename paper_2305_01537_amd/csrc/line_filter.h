@@ -288,7 +288,7 @@ __device__ __forceinline__ void apply_mask(cplx (&v)[NV], int t, int kind, doubl
 // kind (whose phis hold registers): 1/N up to the cutoff, above it the
 // exponential or nothing.  |q| <= c is decided as |q| <= floor(c): c - b rounds
 // where c is small against b, and a sharp line's cutoff just below an integer
-// must not pass as that integer; floor(c) - b is exact.
+// must not pass as that integer; whole numbers are exact.
 template <int N1, int N2, int NV>
 __device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp, double c)
 {
@@ -298,9 +298,9 @@ __device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp,
     static_for<0, 2>([&](auto hh) {
         constexpr int h = decltype(hh)::value;
         // the sequences of exp_factors: |q| = b -+ N2 r + N1 j
-        const double b = (double)(h == 0 ? t : N1 - t);
-        const double room = floor(c) - b;
-        const double e = sharp ? 0.0 : exp(c - b) * inv_n;
+        const int b = h == 0 ? t : N1 - t;
+        const int room = (c < (double)(N1 * N2) ? (int)c : N1 * N2) - b;
+        const double e = sharp ? 0.0 : exp(c - (double)b) * inv_n;
         static_for<0, R>([&](auto rr) {
             constexpr int r = decltype(rr)::value;
             if constexpr (PAD) {
@@ -309,7 +309,7 @@ __device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp,
             const double er = e * exp_int(h == 0 ? -N2 * r : N2 * r);
             static_for<0, N2 / 2>([&](auto jj) {
                 constexpr int j = decltype(jj)::value, k2 = h == 0 ? j : N2 - 1 - j;
-                constexpr double step = (h == 0 ? N2 * r : -N2 * r) + N1 * j;
+                constexpr int step = (h == 0 ? N2 * r : -N2 * r) + N1 * j;
                 cplx &x = v[r * N2 + k2];
                 const double f = room >= step ? inv_n : er * exp_int(-N1 * j);
                 x = cplx{x.re * f, x.im * f};
