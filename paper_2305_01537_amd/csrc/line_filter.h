@@ -183,8 +183,6 @@ __device__ __forceinline__ void gauss_factors(int q0, const GaussChain<N1> &g, U
 constexpr double exp_int(int n)
 {
     return n == 0     ? 1.0
-           : n == 4   ? 5.459815003314423907811026e+1
-           : n == 8   ? 2.980957987041728274743592e+3
            : n == -4  ? 1.831563888873418029371802e-2
            : n == -8  ? 3.354626279025118388213891e-4
            : n == -10 ? 4.539992976248485153559152e-5
@@ -209,26 +207,50 @@ constexpr double exp_int(int n)
                       : __builtin_nan("");
 }
 
-// Exponential factors of one second-stage row, with the 1/N folded in, along
-// the same two sequences as gauss_factors: min(1, exp(c - |q|)) is the mask
-// (eq. exp_filter: 1 up to the cutoff, e^{-(|q| - c)} above), and the
-// exponentials of a sequence are its first member times e^{-N1 j}, so a mode
-// costs a multiplication by a constant and a minimum.  ea and eb: exp(c - t) / N and
-// exp(c - N1 + t) / N, the first members of row t's sequences (t < N2); row
-// t + N2 R takes them times e^{-+N2 R}.  c is at most N/2 (or infinite: then
-// every factor is 1/N), and c - t, c - N1 + t are exact wherever they matter:
-// a difference of two multiples of c's last place that is no larger than
-// they are.
-template <int N1, int N2, int R, typename Use>
+// The exponentials exp(c - |q|) / N of a lane's rows k1 = t + N2 r, r < R, along
+// the two sequences of gauss_factors: exp_seq<H> forms one, where the sequence
+// is nearest to mode 0, and exp_row takes it to the first member of row r, H = 0
+// at |q| = k1 and H = 1 at |q| = N1 - k1, by a constant e^{-k N2}.  So b in c - b
+// is at most N2 and the difference is exact, or below zero and its rounding
+// (relative to c - |q|) damped by the exponential; from H = 1 of row 0 (b up to
+// N1) it came back to modes at the cutoff and put factors up to 1e-15 off.
+template <int N1, int N2, int R>
+__device__ __forceinline__ bool last_row_exists(int t)
+{
+    return N1 == N2 * R || R == 1 || t + N2 * (R - 1) < N1;
+}
+
+template <int N1, int N2, int R, int H>
+__device__ __forceinline__ double exp_seq(double c, int t)
+{
+    const int b = H == 0 ? t : N1 - t - N2 * (last_row_exists<N1, N2, R>(t) ? R - 1 : R - 2);
+    return exp(c - (double)b) * (1.0 / (N1 * N2));
+}
+
+template <int N1, int N2, int R, int H, int r>
+__device__ __forceinline__ double exp_row(double e, int t)
+{
+    constexpr int last = R - 1 - r, before = last > 0 ? last - 1 : 0;
+    if constexpr (H == 0) return e * exp_int(-N2 * r);
+    else if constexpr (N1 == N2 * R) return e * exp_int(-N2 * last);
+    else return e * (last_row_exists<N1, N2, R>(t) ? exp_int(-N2 * last) : exp_int(-N2 * before));
+}
+
+// Exponential factors of one second-stage row, with the 1/N folded in: min(1,
+// exp(c - |q|)) is the mask (eq. exp_filter: 1 up to the cutoff, e^{-(|q| - c)}
+// above), and the exponentials of a sequence are its first member (exp_row: ea,
+// eb) times e^{-N1 j}, so a mode costs a multiplication by a constant and a
+// minimum.
+template <int N1, int N2, typename Use>
 __device__ __forceinline__ void exp_factors(double ea, double eb, Use &&use)
 {
     constexpr double inv_n = 1.0 / (N1 * N2);
     static_for<0, 2>([&](auto hh) {
         constexpr int h = decltype(hh)::value;
-        const double e = h == 0 ? ea * exp_int(-N2 * R) : eb * exp_int(N2 * R);
         static_for<0, N2 / 2>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            use(std::integral_constant<int, h == 0 ? j : N2 - 1 - j>{}, fmin(e * exp_int(-N1 * j), inv_n));
+            use(std::integral_constant<int, h == 0 ? j : N2 - 1 - j>{},
+                fmin((h == 0 ? ea : eb) * exp_int(-N1 * j), inv_n));
         });
     });
 }
@@ -276,9 +298,11 @@ __device__ __forceinline__ void apply_mask(cplx (&v)[NV], int t, int kind, doubl
         const GaussChain<N1> g(c);
         rows([&](auto rr, auto &&use) { gauss_factors<N1, N2>(t + N2 * decltype(rr)::value, g, use); });
     } else if (kind == 0) {
-        constexpr double inv_n = 1.0 / (N1 * N2);
-        const double ea = exp(c - (double)t) * inv_n, eb = exp(c - (double)(N1 - t)) * inv_n;
-        rows([&](auto rr, auto &&use) { exp_factors<N1, N2, decltype(rr)::value>(ea, eb, use); });
+        const double ea = exp_seq<N1, N2, R, 0>(c, t), eb = exp_seq<N1, N2, R, 1>(c, t);
+        rows([&](auto rr, auto &&use) {
+            constexpr int r = decltype(rr)::value;
+            exp_factors<N1, N2>(exp_row<N1, N2, R, 0, r>(ea, t), exp_row<N1, N2, R, 1, r>(eb, t), use);
+        });
     } else {
         rows([&](auto rr, auto &&use) { sharp_factors<N1, N2>(t + N2 * decltype(rr)::value, c, use); });
     }
@@ -297,16 +321,15 @@ __device__ __forceinline__ void apply_mask_two(cplx (&v)[NV], int t, bool sharp,
     constexpr bool PAD = NV != N1;
     static_for<0, 2>([&](auto hh) {
         constexpr int h = decltype(hh)::value;
-        // the sequences of exp_factors: |q| = b -+ N2 r + N1 j
-        const int b = h == 0 ? t : N1 - t;
-        const int room = (c < (double)(N1 * N2) ? (int)c : N1 * N2) - b;
-        const double e = sharp ? 0.0 : exp(c - (double)b) * inv_n;
+        // the two sequences: |q| = t + N2 r + N1 j and N1 - t - N2 r + N1 j
+        const int room = (c < (double)(N1 * N2) ? (int)c : N1 * N2) - (h == 0 ? t : N1 - t);
+        const double e = sharp ? 0.0 : exp_seq<N1, N2, R, h>(c, t);
         static_for<0, R>([&](auto rr) {
             constexpr int r = decltype(rr)::value;
             if constexpr (PAD) {
                 if (t + N2 * r >= N1) return;
             }
-            const double er = e * exp_int(h == 0 ? -N2 * r : N2 * r);
+            const double er = exp_row<N1, N2, R, h, r>(e, t);
             static_for<0, N2 / 2>([&](auto jj) {
                 constexpr int j = decltype(jj)::value, k2 = h == 0 ? j : N2 - 1 - j;
                 constexpr int step = (h == 0 ? N2 * r : -N2 * r) + N1 * j;
@@ -360,7 +383,7 @@ __device__ __forceinline__ void apply_mask_pair(cplx (&v)[NV], int t, int ka, in
     constexpr int R = NV / N2;
     constexpr bool PAD = NV != N1;
     constexpr double inv_n = 1.0 / N;
-    const double ea0 = exp(c - (double)t) * inv_n, eb0 = exp(c - (double)(N1 - t)) * inv_n;
+    const double ea0 = exp_seq<N1, N2, R, 0>(c, t), eb0 = exp_seq<N1, N2, R, 1>(c, t);
     const GaussChain<N1> gc(c);
     const bool ga = ka == 1, gb = kb == 1, sa = ka == 2, sb = kb == 2;
     static_for<0, 2>([&](auto part) {
@@ -386,8 +409,8 @@ __device__ __forceinline__ void apply_mask_pair(cplx (&v)[NV], int t, int ka, in
                 constexpr int k2 = decltype(kk)::value;
                 constexpr bool first = k2 < N2 / 2;
                 constexpr int j = first ? k2 : N2 - 1 - k2;
-                constexpr double steps = exp_int(first ? -N2 * r : N2 * r), step = exp_int(-N1 * j);
-                const double fe = fmin((first ? ea0 : eb0) * steps * step, inv_n);
+                const double e = first ? exp_row<N1, N2, R, 0, r>(ea0, t) : exp_row<N1, N2, R, 1, r>(eb0, t);
+                const double fe = fmin(e * exp_int(-N1 * j), inv_n);
                 const int q = t + N2 * r + N1 * k2, qhat = first ? q : N - q;
                 const double fs = (double)qhat <= c ? inv_n : 0.0;
                 const double fa = ga ? fg : sa ? fs : fe, fb = gb ? fg : sb ? fs : fe;

@@ -19,10 +19,11 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["sharp"])
+@pytest.mark.parametrize("name", ["sharp", "exponential"])
 def test_line_filter(checker, name):
     """sharp: a mode is kept exactly when |q| <= c, for cutoffs up to three
     units of the last place around every integer, at every line length, in
-    both forms of the mask."""
+    both forms of the mask.  exponential: every factor is min(1, e^{c - |q|}) to
+    the roundings that form it, in all three forms."""
     r = subprocess.run([checker, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
