@@ -491,11 +491,10 @@ __device__ __forceinline__ void transpose_bwd(cplx (&v)[NV], int t, double *L)
     });
 }
 
-// v[OFF + k] *= w^k (or conj(w)^k with CONJ) for k in [1, K), where
-// w^j = tw[j * s].  Powers are formed as w^(4a + b) = w^(4a) * w^b from the
-// table entries w^1..w^3 and w^4, w^8, ...: a handful of loads and at most
-// one rounding per twiddle.  Needs (K - 1) * s < N.
-template <int K, bool CONJ, int OFF, int NV>
+// v[k] *= conj(w)^k for k in [1, K), where w^j = tw[j * s].  Powers are formed
+// as w^(4a + b) = w^(4a) * w^b from the table entries w^1..w^3 and w^4, w^8, ...:
+// a handful of loads and at most one rounding per twiddle.  Needs (K - 1) * s < N.
+template <int K, int NV>
 __device__ __forceinline__ void twiddle_powers(cplx (&v)[NV], const Twiddle *__restrict__ tw, int s)
 {
     cplx lo[4], hi[(K + 3) / 4];
@@ -518,7 +517,18 @@ __device__ __forceinline__ void twiddle_powers(cplx (&v)[NV], const Twiddle *__r
         if constexpr (a == 0) w = lo[b];
         else if constexpr (b == 0) w = hi[a];
         else w = cmul(hi[a], lo[b]);
-        v[OFF + k] = CONJ ? cmulc(v[OFF + k], w) : cmul(v[OFF + k], w);
+        v[k] = cmulc(v[k], w);
+    });
+}
+
+// w[k] = w^k, k in [1, K), each from the table.
+template <int K>
+__device__ __forceinline__ void load_twiddles(cplx (&w)[K], const Twiddle *__restrict__ tw, int s)
+{
+    static_for<1, K>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        const Twiddle e = tw[k * s];
+        w[k] = cplx{e.re, e.im};
     });
 }
 
@@ -594,11 +604,29 @@ __device__ __forceinline__ void filter_line(cplx (&v)[NV], int t, int kind, int 
         L += zero;
     }
     static_for<0, R>([&](auto rr) { dft_reg<N2, true, decltype(rr)::value * N2>(v); });
-    transpose_bwd<N1, N2, WAVE>(v, t, L);
     if constexpr ((N1 & (N1 - 1)) == 0) {
+        transpose_bwd<N1, N2, WAVE>(v, t, L);
         dft_twisted<N, N1, true>(v, t, tw_inv);
+    } else if constexpr (N1 % 5 == 0) {
+        transpose_bwd<N1, N2, WAVE>(v, t, L);
+        twiddle_powers<N1>(v, tw_inv, t);
+        dft_reg<N1, true>(v);
     } else {
-        twiddle_powers<N1, true, 0>(v, tw_inv, t);
+        // A product of two entries carries the roundings of both: with them,
+        // lines of 48, 96 and 192 points came out 1 to 5 % further from the
+        // exact filter than with twiddles on both sides of the transposes.  The
+        // loads come before the transpose where they go to memory (two passes,
+        // 800 MB, products / loads: theta 96 points 271 / 264 us, 192 points 283 /
+        // 276, 48 points 418 / 423; phi 305 / 312, 261 / 263, 305 / 311; joined
+        // shells the same).  At 80 and 160 points products are near enough.
+        cplx w[N1];
+        if constexpr (!LEAN) load_twiddles<N1>(w, tw_inv, t);
+        transpose_bwd<N1, N2, WAVE>(v, t, L);
+        if constexpr (LEAN) load_twiddles<N1>(w, tw_inv, t);
+        static_for<1, N1>([&](auto kk) {
+            constexpr int k = decltype(kk)::value;
+            v[k] = cmulc(v[k], w[k]);
+        });
         dft_reg<N1, true>(v);
     }
 }

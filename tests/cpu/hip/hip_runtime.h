@@ -1,5 +1,6 @@
-// The device names that the line filter's headers use, as plain host code for
-// one lane: lets a host compiler take those headers for the CPU tests.
+// The device names that the line filter's headers use, as plain host code: lets a
+// host compiler take those headers for the CPU tests.  A lane is a thread, and
+// the lanes of a wave meet at its barrier (lane_barrier, the including program's).
 #pragma once
 #include <cmath>
 #include <cstddef>
@@ -16,8 +17,10 @@ using std::fmin;
 #define __shared__ static
 #define __forceinline__ inline
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
-#define __builtin_amdgcn_wave_barrier() ((void)0)
+#define __builtin_amdgcn_wave_barrier() lane_barrier()
 #define __builtin_amdgcn_sched_barrier(mask) ((void)0)
+
+void lane_barrier();
 
 struct HostIndex { int x; };
 static HostIndex threadIdx{0}, blockIdx{0}, blockDim{1}, gridDim{1};
