@@ -280,10 +280,10 @@ int apply_overlap(sphfilt_plan p, bool adjoint, double *x, const Decisions &d, h
         return phi_split(p, x, x, p->dev.phi_in, (int)t.phi_in.size(), t.phi_in_hyb, d, s);
     };
     if (e == hipSuccess) e = adjoint ? rings_in() : theta();
-    // the rings of theta-idle shells: never hybrid
+    // the rings of theta-idle shells: never hybrid, but by the kernel instance
+    // that takes them in two passes
     if (e == hipSuccess)
-        e = launch_phi(p->n_phi, p->phi_lines, x, x, p->dev.phi_rest, t.phi_rest_active,
-                       p->n_theta, p->dev.tw_phi, pass_args(p, d.phi, d, false), side);
+        e = phi_split(p, x, x, p->dev.phi_rest, t.phi_rest_active, t.phi_hyb, d, side);
     if (e == hipSuccess) e = adjoint ? theta() : rings_in();
     if (e == hipSuccess) e = hipEventRecord(p->side.join, side);
     if (e == hipSuccess) e = hipStreamWaitEvent(s, p->side.join, 0);
@@ -297,8 +297,8 @@ int apply_overlap(sphfilt_plan p, bool adjoint, double *x, const Decisions &d, h
 // ring workgroups or the phi kernel (all of them out of place, where identity
 // rings are copied), so a point moves once, or twice where its shell takes two
 // passes.  The sets touch different shells; with overlapped passes the last
-// one runs on the side stream.  Every shell takes the same kernels in place and
-// out of place.
+// one runs on the side stream.  Every shell and ring takes the same kernel
+// instances in place, out of place and overlapped: the results are the same bits.
 int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, const Decisions &d,
                  hipStream_t s)
 {
@@ -344,7 +344,8 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
                                pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
     // in place on one stream the phi kernel takes the two-pass shells' rings and
     // the rest's in one launch (phi_rest follows phi_in); where no plain shell
-    // is joined, hybrid and plain shells share the launches
+    // is joined, hybrid and plain shells share the launches (and the rest's rings
+    // take the hybrid-capable instance in a launch of their own, too)
     const bool one_two = n_join == 0 && nh > nj && n_two > 0;
     const bool one_phi = in == out && rest == s && !along && n_two > 0;
     if (e == hipSuccess && nh > nj && !one_two) e = two(nj, nh - nj, true, 0);
@@ -354,7 +355,7 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
     if (e == hipSuccess && n_join > 0) e = join(n_join, along && rest == s ? n_rest : 0, s);
     if (e == hipSuccess && along && rest != s) e = join(0, n_rest, rest);
     if (e == hipSuccess && !along && !one_phi)
-        e = phi(in, (int)t.phi_in.size(), n_rest, false, rest);
+        e = phi(in, (int)t.phi_in.size(), n_rest, one_two, rest);
     if (rest != s) {
         if (e == hipSuccess) e = hipEventRecord(p->side.join, rest);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, p->side.join, 0);

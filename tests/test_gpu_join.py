@@ -276,3 +276,35 @@ def test_two_passes_out_of_place_filter_every_ring(torch_gpu, shape, L, hybrid):
         out.backward(g)
         assert torch.equal(xd.grad, gref)
     plan.close()
+
+
+@pytest.mark.parametrize("shape,L", [((3, 40, 128, 256), 6.0), ((3, 30, 96, 192), 6.0), ((3, 20, 80, 160), 3.0),
+                                     ((3, 12, 64, 96), 3.0)])
+def test_few_plain_shells_beside_hybrid_ones_give_the_same_bits_everywhere(torch_gpu, shape, L):
+    """Too few plain shells for a round beside hybrid shells in two passes (and a
+    grid that is never joined): in place, out of place and with overlapped
+    passes the bits are the same, and the oracle's filter."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Plan
+    F, R, T, P = shape
+    x, parity = fields(shape, 661 + T)
+    x[0] += 3.0
+    x[0, R // 2, : T // 3, 1] = 0.0
+    kind = np.array([HYBRID, EXP, SHARP], dtype=np.int32)
+    plan = Plan(R, T, P, F, parity=parity, L=L, kind=kind)
+    st = plan.stats()
+    assert 0 < st["theta_shells_active"] - R < 2 * R          # plain shells: some filtered, some idle
+    print(f"[gpu] few plain shells {shape}", flush=True)
+    xd = torch.from_numpy(x).cuda()
+    for name, ref_fn in (("apply", oracle.forward), ("apply_adjoint", oracle.adjoint)):
+        call = getattr(plan, name)
+        got = call(xd)
+        for overlap in (0, 2):
+            plan.set_overlap(overlap)
+            y = xd.clone()
+            assert torch.equal(call(y, out=y), got), overlap
+        plan.set_overlap(0)
+        ref = ref_fn(x, parity=parity, L=np.full(F, L), kind=kind)
+        for f in range(F):
+            assert rel(got[f].cpu().numpy(), ref[f]) <= TOL, (name, f)
+    plan.close()
