@@ -217,24 +217,78 @@ bool patch_joinable(const sphfilt_batch b, const PatchHost &p)
            (t.theta_active == t.n_fused || !t.join_c.empty());
 }
 
+// The line lengths whose joinable patches are joined.  The joined launches of the
+// lengths run one after the other, and a launch of few shells takes its latency
+// whatever its bytes; the work list takes all its patches in two launches.  So
+// small sets of unlike patches belong on the list: nine patches of 3 x 4 shells,
+// one of each length, 77 us joined and 27 listed, 3 x 32 shells each of 32, 64, 128
+// and 256 points 52 and 36; but 6 x 128 filtered shells of these four 148 and 203, 64 patches at cal-L = 3 818 and about 1130.  The costs below fit
+// 200 such batches (one to nine lengths, 1 to 768 shells each, both ways) to 6 %
+// root mean square, and the cheaper way by them lost more than 3 % in five of the
+// batches (7 % at most).  A length is listed where its launch would cost more than
+// its two passes on the list, if the list as a whole then pays; lengths with
+// too few shells for a round of one per compute unit always are (join_count).
+std::vector<int> joined_lines(const sphfilt_batch b)
+{
+    struct Class {
+        int n_line;
+        double join, list;               // us, its launch and its items on the list
+    };
+    constexpr double kList = 14.0, kListLong = 2.5;          // us: the list's launches; with 256-point lines
+    constexpr double kJoinRate = 8.8e6, kListRate = 6.6e6;   // bytes per us
+    std::vector<Class> classes;
+    bool listed = false;
+    for (int N : {256, 192, 160, 128, 96, 80, 64, 48, 32}) {
+        long long shells = 0, rings = 0;
+        for (const PatchHost &p : b->patches) {
+            if (p.n_phi != N || !patch_joinable(b, p)) continue;
+            shells += p.tables.theta_active;
+            rings += p.tables.phi_rest_active;
+        }
+        if (shells + rings == 0) continue;
+        if (join_count(N, (int)shells, (int)rings, b->n_cu) == 0) {
+            listed = true;
+            continue;
+        }
+        // a launch's latency; where a workgroup fills a unit, each round's
+        const double latency = N <= 64 ? 7.0 : N <= 128 ? 10.0 : N < 256 ? 13.5 : 20.0;
+        const double rounds = N < 160 ? 1.0 : (double)((shells + b->n_cu - 1) / b->n_cu);
+        const double bytes = 16.0 * ((double)shells * N * N / 2 + 2.0 * (double)rings * N);
+        const double again = 16.0 * (double)shells * N * N / 2;
+        classes.push_back(Class{N, latency * rounds + bytes / kJoinRate,
+                                (bytes + again) / kListRate + (N == 256 ? kListLong : 0.0)});
+    }
+    for (const PatchHost &p : b->patches)
+        listed |= !patch_joinable(b, p) && p.tables.theta_active + p.tables.phi_active > 0;
+    double all = listed ? kList : 0.0, some = kList;
+    for (const Class &c : classes) {
+        all += c.join;
+        some += std::min(c.join, c.list);
+    }
+    std::vector<int> lines;
+    for (const Class &c : classes)
+        if (all <= some || c.join <= c.list) lines.push_back(c.n_line);
+    return lines;
+}
+
+bool patch_joined(const sphfilt_batch b, const PatchHost &p, const std::vector<int> &lines)
+{
+    return patch_joinable(b, p) && std::find(lines.begin(), lines.end(), p.n_phi) != lines.end();
+}
+
 // The joined items of line length N: shells, and the ring pairs of the
 // theta-idle shells, of every joinable patch; shells first, or spread over the
-// first 4/5 of the rings (join_spread).  64 patches of 16 x 32 to 128 x 256 at
-// cal-L = 3: 1952 us as items of the one-kernel schedule with its waits, about
-// 1130 as two launches of fused and two-pass items, 890 joined (4.1 TB/s of
-// 16 B per touched point); 24 patches with radix-3 lines 838 -> 371.  None if the class has too few shells
-// for a round of one per compute unit (join_count): two passes are faster.
+// first 4/5 of the rings (join_spread).
 std::vector<BatchWork> join_items(const sphfilt_batch b, int N, bool all)
 {
     std::vector<BatchWork> shells, rings;
     const int S = join_group_shells(N), L = join_group_rings(N);
-    int n_shells = 0, n_rings = 0;
+    int n_rings = 0;
     for (int pi = 0; pi < (int)b->patches.size(); ++pi) {
         const PatchHost &p = b->patches[(size_t)pi];
         if (p.n_phi != N || !patch_joinable(b, p)) continue;
         const int ns = p.tables.theta_active;
         const int nr = all ? (int)p.tables.phi_rest.size() : p.tables.phi_rest_active;
-        n_shells += ns;
         n_rings += p.tables.phi_rest_active;
         for (int g = 0; g < ns; g += S)
             shells.push_back(BatchWork{pi, 2, 0, p.theta_off + g, (int16_t)std::min(S, ns - g), 0, 0, 0,
@@ -243,7 +297,6 @@ std::vector<BatchWork> join_items(const sphfilt_batch b, int N, bool all)
             rings.push_back(BatchWork{pi, 1, 0, p.phi_rest_off + c, (int16_t)std::min(L, nr - c), 0, 0, 0,
                                       0, 1});
     }
-    if (join_count(N, n_shells, n_rings, b->n_cu) == 0) return {};
     if (!join_spread(N, n_rings, b->n_cu)) {
         shells.insert(shells.end(), rings.begin(), rings.end());
         return shells;
@@ -289,18 +342,13 @@ int build_mode(sphfilt_batch b, int mode)
     std::vector<int> shells;
     // the longest lines first: their workgroups run longest
     m.join.clear();
-    for (int N : {256, 192, 160, 128, 96, 80, 64, 48, 32}) {
+    const std::vector<int> lines = joined_lines(b);
+    for (int N : lines) {
         const std::vector<BatchWork> items = join_items(b, N, !inplace);
-        if (items.empty()) continue;
         m.join.push_back(JoinClass{N, (int)join.size(), (int)items.size()});
         join.insert(join.end(), items.begin(), items.end());
     }
-    auto joined = [&](const PatchHost &p) {
-        if (!patch_joinable(b, p)) return false;
-        for (const JoinClass &c : m.join)
-            if (c.n_line == p.n_phi) return true;
-        return false;
-    };
+    auto joined = [&](const PatchHost &p) { return patch_joined(b, p, lines); };
     // fused shell groups first: they hold a workgroup longest (a whole shell,
     // both passes), so they start before the short items rather than trail them
     for (int p = 0; p < (int)b->patches.size(); ++p)

@@ -308,3 +308,59 @@ def test_few_plain_shells_beside_hybrid_ones_give_the_same_bits_everywhere(torch
         for f in range(F):
             assert rel(got[f].cpu().numpy(), ref[f]) <= TOL, (name, f)
     plan.close()
+
+
+@pytest.mark.parametrize("n_theta,n_r", [(16, 9), (24, 9), (32, 7), (40, 5), (48, 5), (64, 9), (80, 60), (96, 60),
+                                         (128, 60)])
+@pytest.mark.parametrize("adjoint,inplace", [(False, False), (True, True)])
+def test_a_batch_of_one_line_length_is_joined(torch_gpu, n_theta, n_r, adjoint, inplace):
+    """Two patches of one length, plain kinds, filtered and idle shells: joined
+    (from a round of shells on at 160 points and more), against the oracle."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Batch
+    shapes = [(3, n_r, n_theta, 2 * n_theta), (1, n_r + 2, n_theta, 2 * n_theta)]
+    patches, data = [], []
+    for i, shape in enumerate(shapes):
+        x, parity = fields(shape, 700 + i + n_theta)
+        F, R, T, P = shape
+        rho = np.where(np.arange(R) % 5 == 4, 0.3 * T, 0.4)          # a fifth of the shells idle at cal-L = 2
+        patches.append(dict(n_fields=F, n_r=R, n_theta=T, n_phi=P, parity=parity, L=2.0, rho=rho,
+                            kind=np.array([EXP, SHARP, EXP][:F], dtype=np.int32)))
+        data.append(x)
+    batch = Batch(patches)
+    print(f"[gpu] batch of one length {n_theta} adjoint={adjoint}", flush=True)
+    xs = [torch.from_numpy(x).cuda() for x in data]
+    got = batch.apply(xs, outs=xs if inplace else None, adjoint=adjoint)
+    ref_fn = oracle.adjoint if adjoint else oracle.forward
+    for p, x, g in zip(patches, data, got):
+        ref = ref_fn(x, parity=p["parity"], L=np.full(p["n_fields"], 2.0), rho=p["rho"], kind=p["kind"])
+        assert rel(g.cpu().numpy(), ref) <= TOL, p
+    batch.close()
+
+
+def test_small_unlike_patches_are_not_joined(torch_gpu):
+    """A joined launch per length in a row would take longer than the two passes
+    of all patches together: with joining on or off the same kernels run, and
+    give the same bits."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Batch
+    patches, data = [], []
+    for i, T in enumerate((16, 24, 32, 40, 48, 64, 80, 96, 128)):
+        shape = (3, 4, T, 2 * T)
+        x, parity = fields(shape, 760 + i)
+        patches.append(dict(n_fields=3, n_r=4, n_theta=T, n_phi=2 * T, parity=parity, L=3.0,
+                            kind=np.array([EXP, GAUSS, SHARP], dtype=np.int32)))
+        data.append(torch.from_numpy(x).cuda())
+    batch = Batch(patches)
+    print("[gpu] small unlike patches", flush=True)
+    for adjoint in (False, True):
+        on = batch.apply(data, adjoint=adjoint)
+        batch.set_fused(False)
+        off = batch.apply(data, adjoint=adjoint)
+        batch.set_fused(True)
+        for p, x, a, b in zip(patches, data, on, off):
+            assert torch.equal(a, b), p
+            ref = (oracle.adjoint if adjoint else oracle.forward)(
+                x.cpu().numpy(), parity=p["parity"], L=np.full(3, 3.0), kind=p["kind"])
+            assert rel(a.cpu().numpy(), ref) <= TOL, p
+    batch.close()
