@@ -399,8 +399,9 @@ int sphfilt_batch_apply(sphfilt_batch batch, const double *const *ins, double *c
  * Every call on one device shares that device's array: calls that overlap on
  * one device (on different streams, from any batch) race and give wrong
  * results; calls must be ordered on one stream, or synchronised.  The array
- * keeps the last call's contents; each call clears what must start at zero
- * (counters, tickets, error word) with a kernel before its filter kernels.
+ * keeps the last call's contents; each call clears what its kernels need at zero
+ * (counters, tickets, error word), if anything, with a kernel before its filter
+ * kernels.
  * sphfilt_batch_status reports this array's error word when the batch's last
  * call was this one (valid until the next allocation-free call on the device).
  */
