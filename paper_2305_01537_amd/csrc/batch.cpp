@@ -842,12 +842,13 @@ int tune(sphfilt_batch b, const char *cache_path)
     };
     for (int fz = 1; fz >= 0 && !rc; --fz)
         if (fz == 1 || any_fused) split_wpc(fz);
-    // theta tile widths, per line length with two-pass theta work
+    // theta tile widths, per line length with two-pass theta work in the pick so far
+    if (!rc) rc = set_sched(b, best);
+    const std::vector<int> lines = joined_lines(b);
     for (int n : kLines) {
         bool has = false;
         for (const PatchHost &p : b->patches)
-            has |= 2 * p.n_theta == n &&
-                   !(best.fused && (patch_joinable(b, p) || patch_fused(b, p)));
+            has |= 2 * p.n_theta == n && !patch_joined(b, p, lines) && !patch_fused(b, p);
         if (!has) continue;
         const Sched base = best;
         for (int w : {4, 8, 16, 32, 64}) {
