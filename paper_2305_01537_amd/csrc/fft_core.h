@@ -316,6 +316,14 @@ __device__ __forceinline__ void dft_reg(cplx (&v)[NV])
     }
 }
 
+// The twiddle of level h, index j of dft_twisted<N, M> for k.  tw: W_N^i, i < N,
+// then cos and tan of 2 pi i / N, i < N/4, in .re and .im (host_tables.cpp).
+template <int N, int M, int H, int J>
+__device__ __forceinline__ Twiddle twisted_entry(int k, const Twiddle *__restrict__ tw)
+{
+    return H == 1 ? tw[k * (M / 2)] : tw[N + k * (M / (2 * H)) + J * (N / (2 * H))];
+}
+
 // The M-point DFT of v[OFF + n] w^n, w = W_N^k (INV: everything conjugate), M
 // a power of two dividing N and 0 <= k < N / M: the second stage of the
 // four-step transform with its twiddles inside.  Level h (half size) of the
@@ -323,18 +331,18 @@ __device__ __forceinline__ void dft_reg(cplx (&v)[NV])
 // the twiddles cost no operation beyond the butterflies' own six (eight at
 // h = 1, whose angle passes pi/2): 208 operations at M = 16, where the
 // factors' powers (36), the multiplication (60) and the plain transform (168)
-// took 264.  tw: W_N^i, i < N, then cos and tan of 2 pi i / N, i < N/4, in
-// .re and .im (host_tables.cpp); j and j + h/2 share an entry.
-template <int N, int M, bool INV, int OFF = 0, int NV>
-__device__ __forceinline__ void dft_twisted(cplx (&v)[NV], int k, const Twiddle *__restrict__ tw)
+// took 264.  entry(h, j): the twiddle of level h and j < h/2 (twisted_entry); j and
+// j + h/2 share it.
+template <int M, bool INV, int OFF, int NV, typename Entry>
+__device__ __forceinline__ void dft_twisted_by(cplx (&v)[NV], Entry &&entry)
 {
-    static_assert((M & (M - 1)) == 0 && M >= 4 && N % M == 0 && N % 4 == 0, "power-of-two stage");
+    static_assert((M & (M - 1)) == 0 && M >= 4, "power-of-two stage");
     cplx x[M];
     static_for<0, M>([&](auto kk) {
         constexpr int i = decltype(kk)::value;
         x[i] = v[OFF + bitrev(i, ilog2(M))];
     });
-    const Twiddle w1 = tw[k * (M / 2)];
+    const Twiddle w1 = entry(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});
     const double wi = INV ? -w1.im : w1.im;
     static_for<0, M / 2>([&](auto bb) {
         constexpr int p = 2 * decltype(bb)::value;
@@ -348,7 +356,7 @@ __device__ __forceinline__ void dft_twisted(cplx (&v)[NV], int k, const Twiddle 
         constexpr int h = 1 << decltype(st)::value;
         static_for<0, h / 2>([&](auto jj) {
             constexpr int j = decltype(jj)::value;
-            const Twiddle w = tw[N + k * (M / (2 * h)) + j * (N / (2 * h))];
+            const Twiddle w = entry(std::integral_constant<int, h>{}, jj);
             static_for<0, M / (2 * h)>([&](auto bb) {
                 constexpr int p = 2 * h * decltype(bb)::value + j;
                 butterfly_tan<false, INV>(x[p], x[p + h], w.re, w.im);
@@ -359,6 +367,29 @@ __device__ __forceinline__ void dft_twisted(cplx (&v)[NV], int k, const Twiddle 
     static_for<0, M>([&](auto kk) {
         constexpr int i = decltype(kk)::value;
         v[OFF + i] = x[i];
+    });
+}
+
+// The same with the table read where its entries are used.
+template <int N, int M, bool INV, int OFF = 0, int NV>
+__device__ __forceinline__ void dft_twisted(cplx (&v)[NV], int k, const Twiddle *__restrict__ tw)
+{
+    static_assert(N % M == 0 && N % 4 == 0, "a stage of the line");
+    dft_twisted_by<M, INV, OFF>(v, [&](auto h, auto j) {
+        return twisted_entry<N, M, decltype(h)::value, decltype(j)::value>(k, tw);
+    });
+}
+
+// All entries of dft_twisted<N, M> for k, that of (h, j) at w[h/2 + j].
+template <int N, int M>
+__device__ __forceinline__ void load_twisted(Twiddle (&w)[M / 2], int k, const Twiddle *__restrict__ tw)
+{
+    static_for<0, ilog2(M)>([&](auto st) {
+        constexpr int h = 1 << decltype(st)::value;
+        static_for<0, (h + 1) / 2>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            w[h / 2 + j] = twisted_entry<N, M, h, j>(k, tw);
+        });
     });
 }
 
