@@ -580,7 +580,9 @@ __device__ __forceinline__ void filter_line(cplx (&v)[NV], int t, int kind, int 
         dft_twisted_by<N2, false, 0>(v, [&](auto h, auto j) { return w[decltype(h)::value / 2 + decltype(j)::value]; });
     } else {
         transpose_fwd<N1, N2, WAVE>(v, t, L);
-        if constexpr (LEAN) tw += opaque_zero(v[0].re);
+        // twiddles read only now: of phi at 128 points, read earlier and held, they
+        // cost 1 % (800 MB: 306 -> 303.5 us)
+        if constexpr (LEAN || (N == 128 && WAVE && !HYB)) tw += opaque_zero(v[0].re);
         static_for<0, R>([&](auto rr) {
             constexpr int r = decltype(rr)::value;
             // a padded row's twiddles stay inside the table (its result is dropped)
