@@ -106,6 +106,9 @@ void build_items(int n_r, int n_theta, int n_phi, int n_fields, const int *parit
     std::vector<ThetaItem> tf, ta, ti;     // fused, other active, identity shells
     std::vector<PhiItem> pa, pi, ra, ri;   // all rings; rings of unfused shells
     std::vector<PhiItem> rings;
+    std::vector<double> sines((size_t)(n_theta / 2));
+    for (int j = 0; j < n_theta / 2; ++j)
+        sines[(size_t)j] = std::sin(((double)j + 0.5) * kPi / (double)n_theta);
     // hybrid fields first: every list then starts with the hybrid items, which
     // the hybrid-capable kernels take, and the plain kernels take the rest
     std::vector<int> order;
@@ -127,8 +130,7 @@ void build_items(int n_r, int n_theta, int n_phi, int n_fields, const int *parit
             rings.clear();
             bool all_rings = true;
             for (int j = 0; j < n_theta / 2; ++j) {
-                const double s = std::sin(((double)j + 0.5) * kPi / (double)n_theta);
-                double m = 2.0 * rho * s * L;
+                double m = 2.0 * rho * sines[(size_t)j] * L;
                 if (!(m > cut->floor_modes)) m = cut->floor_modes;
                 const bool pid = may_skip && m >= (double)(n_phi / 2);
                 all_rings = all_rings && !pid;

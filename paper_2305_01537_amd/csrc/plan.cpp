@@ -731,9 +731,9 @@ int sphfilt_plan_create(sphfilt_plan *out, int n_r, int n_theta, int n_phi, int 
         if (!rc) rc = upload(&p->dev.phi_in, rings);
         if (!rc) p->dev.phi_rest = p->dev.phi_in + p->host.phi_in.size();
         if (!rc && !p->host.join_c.empty()) {
-            hipDeviceProp_t prop;
-            if (hipGetDeviceProperties(&prop, p->device) != hipSuccess) rc = SPHFILT_EDEVICE;
-            p->compute_units = prop.multiProcessorCount;
+            if (hipDeviceGetAttribute(&p->compute_units, hipDeviceAttributeMultiprocessorCount, p->device) !=
+                hipSuccess)
+                rc = SPHFILT_EDEVICE;
             p->n_join = join_count(n_phi, p->host.theta_active - p->host.theta_hyb,
                                    p->host.phi_rest_active, p->compute_units);
             // hybrid shells of 256-point lines take two passes: the detector and
