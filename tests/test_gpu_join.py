@@ -364,3 +364,35 @@ def test_small_unlike_patches_are_not_joined(torch_gpu):
                 x.cpu().numpy(), parity=p["parity"], L=np.full(3, 3.0), kind=p["kind"])
             assert rel(a.cpu().numpy(), ref) <= TOL, p
     batch.close()
+
+
+@pytest.mark.parametrize("n_theta", [80, 96, 128])
+def test_workgroups_that_loop_over_shells_keep_them_apart(torch_gpu, n_theta):
+    """From eight shells per compute unit on, one workgroup per unit takes many
+    shells with one LDS area: every shell equals the two-pass filter to rounding,
+    and infinities stay inside their shells."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Plan
+    R = 8 * torch.cuda.get_device_properties(0).multi_processor_count + 150
+    shape = (1, R, n_theta, 2 * n_theta)
+    plan = Plan(R, n_theta, 2 * n_theta, 1, parity=-1, L=0.2, rho=np.ones(R))
+    print(f"[gpu] looping workgroups {shape}", flush=True)
+    x = torch.randn(shape, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    hit = [0, 1, 255, 256, 257, 1000, R // 2, R - 151, R - 1]
+    for name in ("apply", "apply_adjoint"):
+        call = getattr(plan, name)
+        got = call(x)
+        plan.set_fused(False)
+        two = call(x)
+        plan.set_fused(True)
+        size = two.abs().amax(dim=(2, 3))
+        assert float(((got - two).abs().amax(dim=(2, 3)) / size).max()) <= TOL_TWO
+        y = x.clone()
+        y[0, hit, 3, 4] = float("inf")
+        bad = call(y)
+        keep = torch.ones(R, dtype=torch.bool, device="cuda")
+        keep[hit] = False
+        assert torch.equal(bad[0, keep], got[0, keep]), name
+        assert not torch.isfinite(bad[0, hit]).flatten(1).all(dim=1).any(), name
+        del got, two, y, bad
+    plan.close()
