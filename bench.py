@@ -161,6 +161,13 @@ def time_loop(torch, fn, bufs, steps, warmup, stream, info=None):
     return t0.elapsed_time(t1) / steps      # ms per call
 
 
+def once_bytes(st, n_phi):
+    """Least bytes of a call in place on an n_phi = 2 n_theta grid with joined or
+    fused shells.  There every ring of a theta-filtered shell is filtered, so the
+    active rings hold every point that a call touches: read and written once."""
+    return 16 * st["phi_rings_active"] * n_phi
+
+
 def _median_rate(fn, points, reps):
     """Median over `reps` runs of points / wall time of fn()."""
     ts = []
@@ -318,8 +325,16 @@ def bench_patches(torch, steps, stream, n_theta_choices=(16, 32, 64, 128), force
     the tuner's; then only the batched forward is timed."""
     import tempfile
     from paper_2305_01537_amd import synth
-    from paper_2305_01537_amd.filter import Batch, Plan
+    from paper_2305_01537_amd.filter import Batch, Plan, workload_stats
     pts = synth.patches(with_values=False, n_theta_choices=n_theta_choices)
+    # every patch is plain on an n_phi = 2 n_theta grid: joined, each touched
+    # point moves once; with joining off, once per pass
+    assert all(p.n_phi == 2 * p.n_theta for p in pts)
+    once = sum(once_bytes(workload_stats(p.n_r, p.n_theta, p.n_phi, p.n_fields, p.parity, p.L, p.rho), p.n_phi)
+               for p in pts)
+
+    def moved(fused, st):
+        return once if fused else st["bytes_forward_inplace"]
     g = torch.Generator(device="cuda").manual_seed(4)
     xs = [torch.randn((p.n_fields, p.n_r, p.n_theta, p.n_phi), dtype=torch.float64, device="cuda",
                       generator=g) for p in pts]
@@ -330,9 +345,9 @@ def bench_patches(torch, steps, stream, n_theta_choices=(16, 32, 64, 128), force
         st = batch.stats()
         ms_b = time_loop(torch, lambda b: batch.apply(b, outs=b), [xs], steps, 3, stream)
         assert batch.status() == 0
-        out = {"patches": len(pts), "algorithmic_bytes": st["bytes_fused_inplace"],
+        out = {"patches": len(pts), "algorithmic_bytes": moved(True, st),
                "batched_forward_ms": ms_b,
-               "batched_GBps": st["bytes_fused_inplace"] / (ms_b * 1e-3) / 1e9,
+               "batched_GBps": moved(True, st) / (ms_b * 1e-3) / 1e9,
                "schedule": batch.get_schedule()}
         batch.close()
         return out
@@ -358,14 +373,14 @@ def bench_patches(torch, steps, stream, n_theta_choices=(16, 32, 64, 128), force
     assert batch.status() == 0
     out = {
         "patches": len(pts), "points": st["n_points"],
-        "algorithmic_bytes": st["bytes_fused_inplace"],
+        "algorithmic_bytes": moved(tuned_fused, st),
         "batched_forward_ms": ms_b, "batched_adjoint_ms": ms_ba, "per_patch_launch_ms": ms_pp,
         "tuned_fused_items": tuned_fused, "shells_fused": st["shells_fused"],
         "other_setting": {"fused_items": not tuned_fused, "forward_ms": ms_alt,
                           "shells_fused": st_alt["shells_fused"],
-                          "algorithmic_bytes": st_alt["bytes_fused_inplace"]},
+                          "algorithmic_bytes": moved(not tuned_fused, st_alt)},
         "batched_points_per_s": st["n_points"] / (ms_b * 1e-3),
-        "batched_GBps": st["bytes_fused_inplace"] / (ms_b * 1e-3) / 1e9,
+        "batched_GBps": moved(tuned_fused, st) / (ms_b * 1e-3) / 1e9,
         "batched_over_per_patch_speedup": ms_pp / ms_b,
         "schedule": sched,
     }
@@ -376,9 +391,9 @@ def bench_patches(torch, steps, stream, n_theta_choices=(16, 32, 64, 128), force
 
 
 def bench_grmhd(torch, steps, stream):
-    """The grmhd grid (24 x 128 x 64 x 128, 201 MB, paper cutoff): shells fit in
-    LDS, so the plan fuses the theta-filtered shells; timed fused and as two
-    passes, forward and adjoint in place.  Five rotated buffers (1 GB) keep the
+    """The grmhd grid (24 x 128 x 64 x 128, 201 MB, paper cutoff): the plan holds
+    each theta-filtered shell in one workgroup for both passes ("fused"); timed so
+    and as two passes, forward and adjoint in place.  Five rotated buffers (1 GB) keep the
     data out of the 256 MB last-level cache."""
     from paper_2305_01537_amd import synth
     from paper_2305_01537_amd.filter import Plan
@@ -465,14 +480,18 @@ def bench_hybrid(torch, w, bufs, steps, stream):
     plan.apply_ex(bufs[0], out=bufs[1], theta_dec=th, phi_dec=ph)
     ms_rep = time_loop(torch, lambda b: plan.apply_ex(b, out=b, theta_dec=th, phi_dec=ph, replay=True),
                        bufs, steps, 3, stream)
+    fused = plan.get_fused()[0]
     plan.close()
+    # the plain fields' shells are joined (a point moves once), the hybrid ones
+    # take two passes
+    moved = once_bytes(st, P) + 16 * 8 * R * T * P if fused else st["bytes_forward_inplace"]
     return {"workload": "share, fields 0..7 hybrid (cal-L 12), 8..23 exponential (cal-L 3)",
             "forward_ms": ms, "forward_recording_ms": ms_rec, "forward_replay_ms": ms_rep,
             "forward_default_schedule_ms": ms_default,
             "theta_pass_ms": ms_theta, "phi_pass_ms": ms_phi, "schedule": schedule,
             "points_per_s": st["n_points"] / (ms * 1e-3),
-            "GBps": st["bytes_forward_inplace"] / (ms * 1e-3) / 1e9,
-            "algorithmic_bytes": st["bytes_forward_inplace"]}
+            "GBps": moved / (ms * 1e-3) / 1e9,
+            "algorithmic_bytes": moved}
 
 
 def bench_mixed_radix(torch, steps, stream):
@@ -502,7 +521,7 @@ def bench_mixed_radix(torch, steps, stream):
             pb = 16 * st["phi_rings_active"] * P
             res[name] = {"cal_L": L, "forward_ms": ms_f,
                          "points_per_s": st["n_points"] / (ms_f * 1e-3),
-                         "step_GBps": st["bytes_forward_inplace"] / (ms_f * 1e-3) / 1e9,
+                         "step_GBps": once_bytes(st, P) / (ms_f * 1e-3) / 1e9,
                          "theta_GBps": tb / (ms_t * 1e-3) / 1e9 if tb else None,
                          "phi_GBps": pb / (ms_p * 1e-3) / 1e9 if pb else None,
                          "active_theta_shells": st["theta_shells_active"],
@@ -710,7 +729,7 @@ def main():
         extra["dense"] = {
             "cal_L": 0.2, "forward_ms": ms_d,
             "points_per_s": points / (ms_d * 1e-3),
-            "GBps": dst["bytes_forward_inplace"] / (ms_d * 1e-3) / 1e9,
+            "GBps": once_bytes(dst, P) / (ms_d * 1e-3) / 1e9,
             "theta_GBps": 16 * points / (ms_dt * 1e-3) / 1e9,
             "phi_GBps": 16 * points / (ms_dp * 1e-3) / 1e9,
         }
