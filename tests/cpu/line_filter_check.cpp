@@ -115,10 +115,10 @@ void exponential()
 // Whole lines through the line filter, a thread per lane, sharp masks, against
 // the circulant in long double: the largest error of a line relative to its
 // largest value, averaged over random lines, is at most `most`.
-template <int N>
+template <int N, int LINES = 2000>
 void line_error(double most)
 {
-    constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2, NV = Split<N>::NV, LINES = 2000;
+    constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2, NV = Split<N>::NV;
     const long double pi = 3.14159265358979323846264338327950288L;
     std::vector<Twiddle> table(N + N / 4);
     std::vector<long double> root(N);
@@ -186,6 +186,10 @@ int main(int argc, char **argv)
     // the errors of the same transforms with all twiddles in full products on
     // both sides of the transposes, and 0.5 % for other compilers' contractions
     else if (!std::strcmp(name, "radix3_lines")) line_error<48>(1.005 * 2.883e-16), line_error<96>(1.005 * 3.016e-16);
-    else return 2;
+    else if (!std::strcmp(name, "other_lines")) {
+        line_error<32>(1.005 * 2.161e-16), line_error<64>(1.005 * 2.634e-16), line_error<80>(1.005 * 2.878e-16);
+        line_error<128, 800>(1.005 * 2.915e-16), line_error<160, 600>(1.005 * 3.185e-16);
+        line_error<256, 400>(1.005 * 3.163e-16);
+    } else return 2;
     return failures ? 1 : 0;
 }

@@ -19,13 +19,13 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("name", ["sharp", "exponential", "radix3_lines"])
+@pytest.mark.parametrize("name", ["sharp", "exponential", "radix3_lines", "other_lines"])
 def test_line_filter(checker, name):
     """sharp: a mode is kept exactly when |q| <= c, for cutoffs up to three
     units of the last place around every integer, at every line length, in
     both forms of the mask.  exponential: every factor is min(1, e^{c - |q|}) to
-    the roundings that form it, in all three forms.  radix3_lines: whole lines
-    of 48 and 96 points are no further from the exact filter on average than
-    with every twiddle multiplied in by itself."""
+    the roundings that form it, in all three forms.  radix3_lines and
+    other_lines: whole lines are no further from the exact filter on average
+    than with every twiddle multiplied in by itself."""
     r = subprocess.run([checker, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
