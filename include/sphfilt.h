@@ -484,18 +484,20 @@ int sphfilt_batch_stats(sphfilt_batch batch, sphfilt_stats *out);
 
 /*
  * Fused and joined shells in a batch (as sphfilt_plan_set_fused): a patch with
- * n_phi = 2 * n_theta and no hybrid field has its theta-filtered shells joined
- * (at 160, 192 and 256 points where the batch has enough of them for a round of
- * one per compute unit); one with hybrid fields and n_phi <= 128 runs them as
- * fused items.  Either way both passes take one HBM round trip, the rings of
- * its other shells go along, and it has no second-pass work.
+ * n_phi = 2 * n_theta and no hybrid field has its theta-filtered shells joined,
+ * where the launch of its line length over all patches costs less than the two
+ * passes of these patches on the work list (batch.cpp, joined_lines: large sets
+ * and sets of one length are, a few small unlike patches are not); one with
+ * hybrid fields and n_phi in {32, 64, 128} runs them as fused items.  Either way
+ * both passes take one HBM round trip, the rings of its other shells go along,
+ * and it has no second-pass work.
  *   enable  1 or 0 (every patch in two passes).  The autotuner times both
  *           (when some patch allows fused items) with every schedule and keeps
  *           the fastest; untuned batches start with 1.
  * Changing it drops the batch's captured graphs and work lists (they are
  * rebuilt on the next call) after synchronising the device.  get_fused
- * reports the setting and the number of shells of n_phi <= 128 it covers (NULL
- * outputs are skipped).
+ * reports the setting and the number of theta-filtered shells of n_phi = 2 *
+ * n_theta in {32, 64, 128} (NULL outputs are skipped).
  */
 int sphfilt_batch_set_fused(sphfilt_batch batch, int enable);
 int sphfilt_batch_get_fused(sphfilt_batch batch, int *enable, int *shells_fused);

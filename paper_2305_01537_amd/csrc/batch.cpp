@@ -7,8 +7,9 @@
 // What the batch adds is scheduling, so that small patches do not leave the GPU
 // idle and one graph launch covers all of them: the shells of plain patches on
 // n_phi = 2 n_theta grids are joined, in one launch per line length over all
-// patches (kernels_join.hip); every other patch's theta groups and ring-pair
-// groups become items of one work list (see batch_kernels.h).
+// patches (kernels_join.hip), where that costs less (joined_lines); every other
+// patch's theta groups and ring-pair groups become items of one work list (see
+// batch_kernels.h).
 #include "../../include/sphfilt.h"
 #include "batch_internal.h"
 #include "host_tables.h"
@@ -670,18 +671,6 @@ struct Sched {
     int fused = 1, split = 1, wpc = -1, theta_tiles = 1, phi_groups = 1;
     std::map<int, int> cols;      // theta line length -> sub-tile width (absent: default)
 };
-
-Sched current(const sphfilt_batch b)
-{
-    Sched c;
-    c.fused = b->fused;
-    c.split = b->split;
-    c.wpc = b->wpc;
-    c.theta_tiles = b->theta_tiles;
-    c.phi_groups = b->phi_groups;
-    c.cols = b->theta_cols;
-    return c;
-}
 
 // The theta sub-tile width of patch p under the batch's tile table: the
 // tuned width for its line length where the patch's grid takes it, else the

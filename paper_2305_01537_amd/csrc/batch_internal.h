@@ -102,8 +102,9 @@ int batch_blocks_per_cu(int variant);
 
 // Joined items (kernels_join.hip): the shells and rings of the patches whose
 // shells are all held whole (n_phi = 2 n_theta, plain kinds), one list and one
-// launch per line length; item blockIdx.x of `work` is a group of shells (pass
-// 2, aux their ring cutoffs) or of ring pairs of theta-idle shells (pass 1).
+// launch per line length; an item of `work` is a group of shells (pass 2, aux
+// their ring cutoffs) or of ring pairs of theta-idle shells (pass 1), and a
+// workgroup takes every grid-th item.
 // They wait for nothing and nothing waits for them.
 hipError_t launch_batch_join(int n_line, bool adjoint, const BatchWork *work, int n_work,
                              const double *const *ins, double *const *outs, const ThetaItem *th,

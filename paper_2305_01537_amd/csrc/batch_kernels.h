@@ -16,9 +16,9 @@
 // additionally turns a logic error into a flagged error instead of a hang.
 //
 // The per-line work is done by the same workers as the per-plan kernels
-// (line_filter.h).  Plain patches on n_phi = 2 n_theta grids are not here: their
-// shells are joined (kernels_join.hip).  A patch with hybrid fields and
-// n_phi = 2 n_theta <= 128 runs its theta-filtered shells as fused items (both
+// (line_filter.h).  Plain patches whose shells are joined (kernels_join.hip,
+// joined_lines in batch.cpp) are not here.  A patch with hybrid fields and
+// n_phi = 2 n_theta in {32, 64, 128} runs its theta-filtered shells as fused items (both
 // passes, one HBM round trip, as a plan does) and the rings of its other shells
 // in the first pass: such a patch has no second-pass work.
 #pragma once
@@ -30,7 +30,7 @@ namespace sphfilt {
 // LDS of the largest worker: the line scratch of every theta/phi group and, in
 // the hybrid-capable instances, the staged shells of the fused worker
 // (ShellShape<128>::lds; plain patches' shells are joined, kernels_join.hip).
-template <int N, bool HYB>
+template <int N>
 constexpr int batch_line_lds()
 {
     return lines_per_256<N>() * line_lds<Split<N>::N1, Split<N>::N2>();
@@ -38,18 +38,18 @@ constexpr int batch_line_lds()
 template <bool HYB, bool MIXED>
 constexpr int batch_lds()
 {
-    constexpr int c = batch_line_lds<128, HYB>() > batch_line_lds<256, HYB>() ? batch_line_lds<128, HYB>()
-                                                                           : batch_line_lds<256, HYB>();
+    constexpr int c = batch_line_lds<128>() > batch_line_lds<256>() ? batch_line_lds<128>()
+                                                                           : batch_line_lds<256>();
     constexpr int a = HYB && ShellShape<128>::lds > c ? ShellShape<128>::lds : c;
-    constexpr int b = batch_line_lds<96, HYB>() > batch_line_lds<192, HYB>() ? batch_line_lds<96, HYB>()
-                                                                          : batch_line_lds<192, HYB>();
+    constexpr int b = batch_line_lds<96>() > batch_line_lds<192>() ? batch_line_lds<96>()
+                                                                          : batch_line_lds<192>();
     return MIXED && b > a ? b : a;
 }
 template <int N, bool MIXED>
 constexpr bool batch_lds_fits()
 {
-    return batch_lds<true, MIXED>() >= batch_line_lds<N, true>() &&
-           batch_lds<false, MIXED>() >= batch_line_lds<N, false>();
+    return batch_lds<true, MIXED>() >= batch_line_lds<N>() &&
+           batch_lds<false, MIXED>() >= batch_line_lds<N>();
 }
 static_assert(batch_lds_fits<32, false>() && batch_lds_fits<64, false>() &&
                   batch_lds_fits<128, false>() && batch_lds_fits<256, false>() &&

@@ -54,12 +54,13 @@ __device__ __forceinline__ void join_group(const double *in, double *out, const 
 // per wave and pass, 40 % of the issue slots), a quarter waits for the load and
 // the store, and the LDS is busy for a third; nothing else runs on the unit
 // meanwhile.  Against two passes, whose bound is HBM: 24 x 256 shells of
-// 128 x 256, all filtered, 1087 -> 820 us forward (3.9 TB/s of 16 B per point),
-// 1090 -> 855 adjoint; at cal-L = 3, 187 -> 157.  Shorter lines fit two to six
+// 128 x 256, all filtered, 1090 -> 745 us forward (4.3 TB/s of 16 B per point),
+// 1095 -> 750 adjoint; at cal-L = 3, 187 -> 150.  Shorter lines fit two to six
 // workgroups per unit and come near the bandwidth: all filtered, 24 x 3600
-// shells of 24 x 48 754 -> 355 us, 24 x 1300 of 40 x 80 725 -> 503, 24 x 900 of
-// 48 x 96 573 -> 345, 24 x 508 of 64 x 128 413 -> 325 (in LDS), 24 x 160 of 80 x
-// 160 308 -> 260, 24 x 128 of 96 x 192 330 -> 265.
+// shells of 24 x 48 755 -> 365 us, 24 x 1300 of 40 x 80 723 -> 499, 24 x 900 of
+// 48 x 96 577 -> 346, 24 x 508 of 64 x 128 412 -> 331 (in LDS before), 24 x 160 of
+// 80 x 160 307 -> 232, 24 x 128 of 96 x 192 333 -> 238.  At 128 points six registers
+// (eight in batches) spill under the cap of four waves.
 template <int N, bool ADJ>
 __global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N>())))
 void join_kernel(const double *in, double *out, const ThetaItem *__restrict__ shells,
@@ -89,8 +90,8 @@ void join_kernel(const double *in, double *out, const ThetaItem *__restrict__ sh
 
 // Hybrid shells only: the detector runs on the registers, in both layouts.  A
 // third of the 24 fields hybrid, against two passes: 128 shells of 24 x 48 38.5
-// -> 25 us, of 48 x 96 71 -> 44, of 64 x 128 78 -> 65 (against the form through
-// LDS), of 40 x 80 63 -> 53, of 96 x 192 222 -> 203.
+// -> 25 us, of 48 x 96 71 -> 44, of 64 x 128 81 -> 70 (against the form through
+// LDS), of 40 x 80 63 -> 53, of 96 x 192 222 -> 195, 160 of 80 x 160 171 -> 152.
 template <int N, bool ADJ>
 __global__ __launch_bounds__(JoinShape<N>::width) __attribute__((amdgpu_waves_per_eu(join_waves<N, true>())))
 void join_hybrid_kernel(const double *in, double *out, const ThetaItem *__restrict__ shells,
@@ -210,7 +211,8 @@ int join_count(int n_line, int n, int n_rings, int compute_units)
 // spread shells overlap the two; but they also start later, which pays only
 // where the rings run for several rounds: from two full rounds on (24 x 256
 // shells of 128 x 256 at cal-L = 3, 3.4 rounds: 157 us spread, 176 shells
-// first, 166 as two launches; 24 x 128 of 96 x 192 at cal-L = 2, 2.6 rounds:
+// first, 166 as two launches: of an earlier form, 150 now; 24 x 128 of 96 x 192 at
+// cal-L = 2, 2.6 rounds:
 // 88 / 93 / 102; 24 x 160 of 80 x 160 at cal-L = 4, 1.7 rounds: 43 / 40 / 42).
 bool join_spread(int n_line, int n_rings, int compute_units)
 {

@@ -1320,8 +1320,7 @@ constexpr int pass_lds()
         constexpr int waves = (LINES * Split<N>::N2 + 63) / 64;
         constexpr int all = 160 * 1024 - 4096;            // flags and granularity beside it
         constexpr int part = all / units * waves / 8;
-        constexpr int most = 60 * 1024 / 8;               // a static array's limit is 64 KB
-        return need > part ? need : part < most ? part : most > need ? most : need;
+        return need > part ? need : part;
     }
 }
 

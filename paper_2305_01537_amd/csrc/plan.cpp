@@ -736,10 +736,11 @@ int sphfilt_plan_create(sphfilt_plan *out, int n_r, int n_theta, int n_phi, int 
                 rc = SPHFILT_EDEVICE;
             p->n_join = join_count(n_phi, p->host.theta_active - p->host.theta_hyb,
                                    p->host.phi_rest_active, p->compute_units);
-            // hybrid shells of 256-point lines take two passes: the detector and
-            // the Gaussian make a joined round 51 us of arithmetic, as long as
-            // the passes (share with 8 hybrid fields: 512 us either way; at 192
-            // 203 joined, 207 in two passes)
+            // hybrid shells of 256-point lines take two passes: a joined round is
+            // 51 us, as long as the passes (share with 8 hybrid fields: 512 us
+            // either way; at 192 203 joined, 207 in two passes), with the detector
+            // and the Gaussian and with 66 to 73 registers spilled under the cap
+            // of 128 that 1024 lanes leave
             p->n_join_hyb = n_phi == 256 ? 0 : join_count(n_phi, p->host.theta_hyb, 0, p->compute_units);
         }
     } catch (const std::bad_alloc &) {

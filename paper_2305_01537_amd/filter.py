@@ -266,7 +266,8 @@ class Batch:
     tune_cache: path of a JSON schedule cache; None = default schedule.  A
     patch set not yet in the cache is autotuned (on scratch fields) at
     creation and recorded.
-    Each patch is filtered exactly as by its own Plan (bit-identical results).
+    Each patch is filtered as by its own Plan (equal to rounding; see
+    sphfilt_batch_create).
     """
 
     def __init__(self, patches, tune_cache: Optional[str] = None):
