@@ -369,14 +369,18 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
 // of saved traffic on (32 bytes per point of such a ring that is filtered): 144
 // MB saved 471 -> 373 us (24 x 256 shells of 128 x 160 at cal-L = 3), 219 MB 132 ->
 // 103, 586 MB 409 -> 308, but 55 MB 34 -> 43 and 48 MB 68 -> 72.  (The adjoint's
-// first pass reads every ring once as it is.)  Not on grids with fused shells
-// (reached there with fusing off): phi_in leaves the rings of fused shells out.
-constexpr long long kDirectMinBytes = 96LL << 20;
+// first pass reads every ring once as it is.)  On grids that are joined, but have
+// too few shells to join, it pays from 32 MiB on (128 x 256, 96 x 192, 80 x 160:
+// 26 MiB 49.4 / 48.3 us direct / in two launches, 29 46.3 / 42.5, 32 40.4 / 45.5,
+// 40 68.4 / 69.4, 50 90 / 97, 76 89.6 / 102).  Not on grids with fused shells (reached
+// there with fusing off): phi_in leaves the rings of fused shells out.
+constexpr long long kDirectMinBytes = 96LL << 20, kDirectMinBytesJoined = 32LL << 20;
 
 bool rings_direct(const sphfilt_plan p)
 {
     return p->host.n_fused == 0 && !p->theta_mfma &&
-           32LL * p->host.phi_rest_active * p->n_phi >= kDirectMinBytes;
+           32LL * p->host.phi_rest_active * p->n_phi >=
+               (p->host.join_c.empty() ? kDirectMinBytes : kDirectMinBytesJoined);
 }
 
 int apply_direct(sphfilt_plan p, const double *in, double *out, const Decisions &d, hipStream_t s)
@@ -404,7 +408,9 @@ int apply_two(sphfilt_plan p, Pass first, Pass second, const double *in, double 
         rc = apply_fused(p, first == Pass::Phi, in, out, d, s);
         if (rc != SPHFILT_EUNSUPPORTED) return rc;
     }
-    if (p->fused && !p->host.join_c.empty()) return apply_joined(p, first == Pass::Phi, in, out, d, s);
+    // with nothing to join, two passes below (in a third launch, the rings apart: 2 x
+    // 246 shells of 80 x 160 at cal-L = 0.896 out of place 31 -> 38 us)
+    if (p->fused && p->n_join + p->n_join_hyb > 0) return apply_joined(p, first == Pass::Phi, in, out, d, s);
     if (overlap_pays(p) && in == out) {
         rc = apply_overlap(p, first == Pass::Phi, out, d, s);
         if (rc != SPHFILT_EUNSUPPORTED) return rc;

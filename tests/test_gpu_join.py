@@ -396,3 +396,31 @@ def test_workgroups_that_loop_over_shells_keep_them_apart(torch_gpu, n_theta):
         assert not torch.isfinite(bad[0, hit]).flatten(1).all(dim=1).any(), name
         del got, two, y, bad
     plan.close()
+
+
+@pytest.mark.parametrize("shape,L", [((2, 246, 80, 160), 0.896), ((4, 256, 128, 256), 3.0), ((3, 130, 96, 192), 2.0)])
+def test_too_few_shells_to_join_out_of_place(torch_gpu, shape, L):
+    """Too few filtered shells for a round, the rings of many idle ones: two
+    passes, or with the rings straight from the input; the bits of the call in
+    place, and the oracle's filter on sampled shells."""
+    torch = torch_gpu
+    from paper_2305_01537_amd.filter import Plan
+    F, R, T, P = shape
+    x = np.random.default_rng(811).standard_normal(shape)
+    parity = np.where(np.arange(F) % 2 == 0, 1, -1).astype(np.int32)
+    kind = np.where(np.arange(F) % 2 == 0, EXP, SHARP).astype(np.int32)
+    plan = Plan(R, T, P, F, parity=parity, L=L, kind=kind)
+    n = plan.stats()["theta_shells_active"]
+    print(f"[gpu] too few shells to join {shape}: {n}", flush=True)
+    assert 0 < 16 * n < 9 * torch.cuda.get_device_properties(0).multi_processor_count
+    xd = torch.from_numpy(x).cuda()
+    shells = [0, 1, R // 8, R // 4, R // 2, R - 1]
+    for name, ref_fn in (("apply", oracle.forward), ("apply_adjoint", oracle.adjoint)):
+        got = getattr(plan, name)(xd)
+        y = xd.clone()
+        assert torch.equal(getattr(plan, name)(y, out=y), got), name
+        ref = ref_fn(x[:2, shells], parity=parity[:2], L=np.full(2, L), rho=synth.uniform_rho(R)[shells],
+                     kind=kind[:2])
+        for f in range(2):
+            assert rel(got[f, shells].cpu().numpy(), ref[f]) <= TOL, (name, f)
+    plan.close()
