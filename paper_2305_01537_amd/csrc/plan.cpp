@@ -72,7 +72,7 @@ struct sphfilt_plan_s {
     int overlap;            // 0 off, 1 auto, 2 always: independent rings on the side stream
     HybridArgs hybrid;      // detector parameters; dec / replay set per call
     int compute_units;
-    int n_join;             // joined plain shells: theta items [theta_hyb, theta_hyb + n_join)
+    int n_join;             // joined plain shells: the last n_join active theta items
     int n_join_hyb;         // joined hybrid shells: theta items [0, n_join_hyb)
     SideStream side;
     uint64_t params_hash;   // grid, fields and cutoffs (the tune cache key, with the GPU arch)
@@ -303,8 +303,8 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
                  hipStream_t s)
 {
     const HostTables &t = p->host;
-    const int nh = t.theta_hyb, lines = p->n_theta / 2, n_join = p->n_join;
-    const int done = nh + n_join, n_two = t.theta_active - done;
+    const int nh = t.theta_hyb, nj = p->n_join_hyb, lines = p->n_theta / 2, n_join = p->n_join;
+    const int first_join = t.theta_active - n_join, n_two = first_join - nj;
     const int n_rest = in == out ? t.phi_rest_active : (int)t.phi_rest.size();
     const bool along = n_join > 0;
     std::unique_lock<std::mutex> lock(p->side.m, std::defer_lock);
@@ -325,37 +325,28 @@ int apply_joined(sphfilt_plan p, bool adjoint, const double *in, double *out, co
                           p->dev.tw_phi, pass_args(p, d.phi, d, hybrid), st);
     };
     auto join = [&](int n, int n_rings, hipStream_t st) {
-        return launch_join(adjoint, p->n_phi, in, out, p->dev.theta + nh,
-                           p->dev.join_c + (size_t)nh * lines, n, p->dev.phi_rest, n_rings,
+        return launch_join(adjoint, p->n_phi, in, out, p->dev.theta + first_join,
+                           p->dev.join_c + (size_t)first_join * lines, n, p->dev.phi_rest, n_rings,
                            p->compute_units, p->dev.tw_phi, st);
     };
-    // two passes of shells [first, first + n), whose rings are phi_in's
-    auto two = [&](int first, int n, bool hybrid, int more_rings) {
-        hipError_t r = adjoint ? phi(in, first * lines, n * lines + more_rings, hybrid, s)
-                               : theta(in, first, n, hybrid);
-        if (r == hipSuccess)
-            r = adjoint ? theta(out, first, n, hybrid)
-                        : phi(out, first * lines, n * lines + more_rings, hybrid, s);
-        return r;
-    };
-    const int nj = p->n_join_hyb;
     if (e == hipSuccess && nj > 0)
         e = launch_join_hybrid(adjoint, p->n_phi, in, out, p->dev.theta, p->dev.join_c, nj, p->dev.tw_phi,
                                pass_args(p, d.theta, d, true), pass_args(p, d.phi, d, true), s);
-    // in place on one stream the phi kernel takes the two-pass shells' rings and
-    // the rest's in one launch (phi_rest follows phi_in); where no plain shell
-    // is joined, hybrid and plain shells share the launches (and the rest's rings
-    // take the hybrid-capable instance in a launch of their own, too)
-    const bool one_two = n_join == 0 && nh > nj && n_two > 0;
+    // two passes of the shells in between, hybrid and plain ones in the same
+    // launches, whose rings are phi_in's.  In place on one stream, and where no
+    // plain shell is joined, the phi kernel takes the rest's rings in the same
+    // launch (phi_rest follows phi_in); apart, they take the same instance.
+    const bool hybrid = nh > nj;
     const bool one_phi = in == out && rest == s && !along && n_two > 0;
-    if (e == hipSuccess && nh > nj && !one_two) e = two(nj, nh - nj, true, 0);
-    if (e == hipSuccess)
-        e = one_two ? two(nj, t.theta_active - nj, true, one_phi ? n_rest : 0)
-                    : two(done, n_two, false, one_phi ? n_rest : 0);
+    if (n_two > 0) {
+        const int rings = n_two * lines + (one_phi ? n_rest : 0);
+        if (e == hipSuccess) e = adjoint ? phi(in, nj * lines, rings, hybrid, s) : theta(in, nj, n_two, hybrid);
+        if (e == hipSuccess) e = adjoint ? theta(out, nj, n_two, hybrid) : phi(out, nj * lines, rings, hybrid, s);
+    }
     if (e == hipSuccess && n_join > 0) e = join(n_join, along && rest == s ? n_rest : 0, s);
     if (e == hipSuccess && along && rest != s) e = join(0, n_rest, rest);
     if (e == hipSuccess && !along && !one_phi)
-        e = phi(in, (int)t.phi_in.size(), n_rest, one_two, rest);
+        e = phi(in, (int)t.phi_in.size(), n_rest, hybrid && n_two > 0, rest);
     if (rest != s) {
         if (e == hipSuccess) e = hipEventRecord(p->side.join, rest);
         if (e == hipSuccess) e = hipStreamWaitEvent(s, p->side.join, 0);
@@ -737,17 +728,30 @@ int sphfilt_plan_create(sphfilt_plan *out, int n_r, int n_theta, int n_phi, int 
         if (!rc) rc = upload(&p->dev.phi_in, rings);
         if (!rc) p->dev.phi_rest = p->dev.phi_in + p->host.phi_in.size();
         if (!rc && !p->host.join_c.empty()) {
-            if (hipDeviceGetAttribute(&p->compute_units, hipDeviceAttributeMultiprocessorCount, p->device) !=
-                hipSuccess)
+            const HostTables &t = p->host;
+            int units = 0;
+            if (hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess ||
+                units <= 0) {
                 rc = SPHFILT_EDEVICE;
-            p->n_join = join_count(n_phi, p->host.theta_active - p->host.theta_hyb,
-                                   p->host.phi_rest_active, p->compute_units);
-            // hybrid shells of 256-point lines take two passes: a joined round is
-            // 51 us, as long as the passes (share with 8 hybrid fields: 512 us
-            // either way; at 192 203 joined, 207 in two passes), with the detector
-            // and the Gaussian and with 66 to 73 registers spilled under the cap
-            // of 128 that 1024 lanes leave
-            p->n_join_hyb = n_phi == 256 ? 0 : join_count(n_phi, p->host.theta_hyb, 0, p->compute_units);
+            } else {
+                p->compute_units = units;
+                p->n_join = join_count(n_phi, t.theta_active - t.theta_hyb, t.phi_rest_active, units);
+                // hybrid shells of 256-point lines take two passes: a joined round
+                // is 51 us, as long as the passes (share with 8 hybrid fields: 512
+                // us either way; at 192 203 joined, 207 in two passes), with the
+                // detector and the Gaussian and with 66 to 73 registers spilled
+                // under the cap of 128 that 1024 lanes leave
+                p->n_join_hyb = n_phi == 256 ? 0 : join_count(n_phi, t.theta_hyb, 0, units);
+                // beside plain shells in two passes, hybrid ones in the same launches
+                // save theirs, and joining pays only for rounds of 192 points that are
+                // nearly full (one hybrid field and one plain one, joined / not: 80 x
+                // 160, 150 shells each 36 / 24 us, 256 38.5 / 34.7, 400 60 / 48; 96 x
+                // 192, 200 44 / 40, 256 46 / 48, 400 71 / 65, 1000 125 / 131)
+                const int last = t.theta_hyb % units;
+                if (p->n_join == 0 && t.theta_active > t.theta_hyb &&
+                    !(n_phi == 192 && (last == 0 || 8 * last >= 7 * units)))
+                    p->n_join_hyb = 0;
+            }
         }
     } catch (const std::bad_alloc &) {
         rc = SPHFILT_ENOMEM;

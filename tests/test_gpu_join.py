@@ -279,11 +279,13 @@ def test_two_passes_out_of_place_filter_every_ring(torch_gpu, shape, L, hybrid):
 
 
 @pytest.mark.parametrize("shape,L", [((3, 40, 128, 256), 6.0), ((3, 30, 96, 192), 6.0), ((3, 20, 80, 160), 3.0),
-                                     ((3, 12, 64, 96), 3.0)])
+                                     ((3, 12, 64, 96), 3.0), ((3, 150, 80, 160), 3.0), ((3, 256, 96, 192), 3.0),
+                                     ((3, 142, 80, 160), 0.284)])
 def test_few_plain_shells_beside_hybrid_ones_give_the_same_bits_everywhere(torch_gpu, shape, L):
-    """Too few plain shells for a round beside hybrid shells in two passes (and a
-    grid that is never joined): in place, out of place and with overlapped
-    passes the bits are the same, and the oracle's filter."""
+    """Too few plain shells for a round beside hybrid shells in two passes, a full
+    round of joined ones, a round of plain ones with more behind it (and a grid
+    that is never joined): in place, out of place and with overlapped passes the
+    bits are the same, and the oracle's filter."""
     torch = torch_gpu
     from paper_2305_01537_amd.filter import Plan
     F, R, T, P = shape
